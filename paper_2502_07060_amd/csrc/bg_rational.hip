@@ -18,15 +18,11 @@
 // none.  A fraction with |a| <= B, 0 < b <= B, gcd(a, b) = 1 and a = b x
 // (mod M) is unique (2 B^2 < M) and is what this returns.
 //
-// Limb arithmetic.  Numbers are K 32-bit limbs (K >= number of primes, so
-// M < 2^(31 K)); the Euclidean cofactors t_j are kept in two's complement
-// modulo 2^(32 K), which is exact because |t_j| <= M < 2^(32 K - 1).  Every
-// limb loop is unrolled over K (no run-time register indexing).  A quotient
-// is estimated from the two remainders converted to binary64 (M < 2^992 is
-// within range, relative error below 2^-52): below 2^31 it is taken whole and
-// corrected by at most a few units; larger quotients are removed in pieces of
-// 64 bits aligned to a limb, each an under-estimate, so a remainder never
-// goes negative there.
+// Limb arithmetic.  The remainders are K 32-bit limbs (K >= number of primes,
+// so M < 2^(31 K)).  The cofactors alternate in sign, so their magnitudes are
+// kept, with the sign of t_j aside; |t_j| <= M / r_{j-1} < M / B, so
+// K / 2 + 1 limbs hold them.  Every limb loop is unrolled over K (no run-time
+// register indexing).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -147,8 +143,10 @@ __global__ __launch_bounds__(256) void residue_kernel(ResidueArgs a) {
 // ---------------------------------------------------------------------------
 // Chinese remaindering and rational reconstruction
 // ---------------------------------------------------------------------------
+constexpr int kPairs = BG_RR_MAX_PRIMES * (BG_RR_MAX_PRIMES - 1) / 2;
+
 struct PrimeConst {
-  int32_t p, h, c32, c64, r2, minv;  // minv = (p_0 ... p_{i-1})^-1 R mod p_i
+  int32_t p, c32, minv;  // minv = (p_0 ... p_{i-1})^-1 2^64 mod p_i, balanced
   uint32_t pinv;
 };
 
@@ -159,42 +157,48 @@ struct RRArgs {
   uint8_t* status;
   int64_t npts, ld;
   int nprimes, L;
+  double B_double;
   PrimeConst pc[BG_RR_MAX_PRIMES];
+  int32_t w[kPairs];  // w[i (i - 1) / 2 + j] = -(p_0 ... p_{j-1}) mod p_i, balanced (j < i)
   uint32_t M[BG_RR_MAX_PRIMES];
-  uint32_t B[BG_RR_MAX_PRIMES];
+  uint32_t B[BG_RR_MAX_PRIMES / 2 + 1];
 };
 
 __device__ __forceinline__ FpConst fpc(const PrimeConst& c) {
   FpConst F{};
   F.p = c.p;
-  F.h = c.h;
   F.pinv = c.pinv;
   F.negp = -c.p;
   F.c32 = c.c32;
-  F.c64 = c.c64;
-  F.one = c.c64;
   return F;
 }
 
-// x < 2^31 -> x R mod p (Montgomery form, balanced)
-__device__ __forceinline__ int32_t mont_small(int32_t x, const FpConst& F, int32_t r2) {
-  return fp_mul(fp_norm(x, F), r2, F);
+// x <= B, for B of KT limbs
+template <int K, int KT>
+__device__ __forceinline__ bool not_above(const uint32_t (&x)[K], const uint32_t* B) {
+  uint32_t high = 0;
+#pragma unroll
+  for (int k = KT; k < K; ++k) high |= x[k];
+  int64_t borrow = 0;
+#pragma unroll
+  for (int k = 0; k < (KT < K ? KT : K); ++k) borrow = ((int64_t)B[k] - (int64_t)x[k] + borrow) >> 32;
+  return high == 0 && borrow == 0;
 }
 
 template <int K>
-__device__ __forceinline__ int cmp(const uint32_t (&x)[K], const uint32_t (&y)[K]) {
-  int c = 0;
+__device__ __forceinline__ bool below(const uint32_t (&x)[K], const uint32_t (&y)[K]) {
+  int64_t borrow = 0;
 #pragma unroll
-  for (int k = K - 1; k >= 0; --k)
-    if (c == 0) c = (x[k] > y[k]) - (x[k] < y[k]);
-  return c;
+  for (int k = 0; k < K; ++k) borrow = ((int64_t)x[k] - (int64_t)y[k] + borrow) >> 32;
+  return borrow != 0;
 }
 
+// relative error below K 2^-53 (one rounding a limb)
 template <int K>
 __device__ __forceinline__ double to_double(const uint32_t (&x)[K]) {
-  double v = 0.0;
+  double v = (double)x[K - 1];
 #pragma unroll
-  for (int k = K - 1; k >= 0; --k) v = v * 4294967296.0 + (double)x[k];
+  for (int k = K - 2; k >= 0; --k) v = __builtin_fma(v, 4294967296.0, (double)x[k]);
   return v;
 }
 
@@ -213,6 +217,18 @@ __device__ __forceinline__ int64_t submul(uint32_t (&x)[K], const uint32_t (&y)[
     borrow = diff >> 32;
   }
   return borrow - (int64_t)carry;
+}
+
+// x += c y (mod 2^(32K))
+template <int K>
+__device__ __forceinline__ void addmul(uint32_t (&x)[K], const uint32_t (&y)[K], uint32_t c) {
+  uint64_t carry = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint64_t s = (uint64_t)c * y[k] + ((uint64_t)x[k] + carry);  // < 2^64
+    x[k] = (uint32_t)s;
+    carry = s >> 32;
+  }
 }
 
 template <int K>
@@ -239,6 +255,38 @@ __device__ __forceinline__ void shift_limbs(const uint32_t (&y)[K], int s, uint3
   }
 }
 
+// (x, y) <- (a x - b y, d y - c x), both results in [0, 2^(32K)); a, b, c, d < 2^26
+template <int K>
+__device__ __forceinline__ void mix_sub(uint32_t (&x)[K], uint32_t (&y)[K], uint32_t a, uint32_t b, uint32_t c,
+                                        uint32_t d) {
+  int64_t cx = 0, cy = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint64_t X = (uint64_t)a * x[k] + (uint64_t)cx - (uint64_t)b * y[k];
+    const uint64_t Y = (uint64_t)d * y[k] + (uint64_t)cy - (uint64_t)c * x[k];
+    x[k] = (uint32_t)X;
+    y[k] = (uint32_t)Y;
+    cx = (int64_t)X >> 32;
+    cy = (int64_t)Y >> 32;
+  }
+}
+
+// (x, y) <- (a x + b y, d y + c x)
+template <int K>
+__device__ __forceinline__ void mix_add(uint32_t (&x)[K], uint32_t (&y)[K], uint32_t a, uint32_t b, uint32_t c,
+                                        uint32_t d) {
+  uint64_t cx = 0, cy = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint64_t X = (uint64_t)a * x[k] + cx + (uint64_t)b * y[k];
+    const uint64_t Y = (uint64_t)d * y[k] + cy + (uint64_t)c * x[k];
+    x[k] = (uint32_t)X;
+    y[k] = (uint32_t)Y;
+    cx = X >> 32;
+    cy = Y >> 32;
+  }
+}
+
 template <int K>
 __device__ __forceinline__ void negate(uint32_t (&x)[K]) {
   uint64_t carry = 1;
@@ -250,158 +298,207 @@ __device__ __forceinline__ void negate(uint32_t (&x)[K]) {
   }
 }
 
+// whether p divides x: the limbs from the lowest up, each step a REDC of the
+// sum so far (a division by 2^32 mod p); |sum| < 2^33, the last REDC balanced
 template <int K>
-__device__ __forceinline__ bool is_zero(const uint32_t (&x)[K]) {
-  uint32_t o = 0;
+__device__ __forceinline__ bool divisible(const uint32_t (&x)[K], const FpConst& F) {
+  int64_t s = (int64_t)x[0];
 #pragma unroll
-  for (int k = 0; k < K; ++k) o |= x[k];
-  return o == 0;
+  for (int k = 1; k < K; ++k) s = (int64_t)fp_redc1(s, F) + (int64_t)x[k];
+  return fp_redc1((int64_t)fp_redc1(s, F), F) == 0;
 }
 
-// |x| mod p for x < 2^(32K): sum of limb_k 2^(32k) R, folded, then one REDC
-template <int K>
-__device__ __forceinline__ int32_t mod_prime(const uint32_t (&x)[K], const FpConst& F, int32_t c32m) {
-  int64_t T = 0;
-  int32_t w = F.one;  // 2^(32k) R mod p
+// One Euclidean step on the whole numbers, for a quotient that the leading
+// bits do not settle: (r0, r1) <- (r1, r0 mod r1), the cofactors likewise;
+// a quotient of 2^31 or more is only begun (r0 less a multiple of r1).
+template <int K, int KT>
+__device__ __forceinline__ void full_step(uint32_t (&r0)[K], uint32_t (&r1)[K], uint32_t (&t0)[KT],
+                                          uint32_t (&t1)[KT], bool& neg, double qe) {
+  if (qe < 2147483648.0) {
+    uint32_t qq = (uint32_t)qe;
+    int64_t bo = submul(r0, r1, qq);
+    while (bo < 0) {  // over-estimate: add r1 back
+      uint64_t carry = 0;
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    T = fp_fold(T + (int64_t)x[k] * (int64_t)w, F);
-    w = fp_mul(w, c32m, F);
+      for (int k = 0; k < K; ++k) {
+        const uint64_t s = (uint64_t)r0[k] + r1[k] + carry;
+        r0[k] = (uint32_t)s;
+        carry = s >> 32;
+      }
+      bo += (int64_t)carry;
+      --qq;
+    }
+    while (!below(r0, r1)) {  // under-estimate
+      sub_from(r0, r1);
+      ++qq;
+    }
+    addmul(t0, t1, qq);
+    neg = !neg;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t a0 = r0[k];
+      r0[k] = r1[k];
+      r1[k] = a0;
+    }
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+      const uint32_t b0 = t0[k];
+      t0[k] = t1[k];
+      t1[k] = b0;
+    }
+  } else {
+    // take c 2^(32 s) out of the quotient, c < 2^64 an under-estimate
+    int e = 0;
+    (void)frexp(qe, &e);  // qe in [2^(e-1), 2^e)
+    const int s = e > 64 ? (e - 64 + 31) / 32 : 0;
+    const double scaled = ldexp(qe, -32 * s) * (1.0 - 0x1p-40);
+    uint64_t c = scaled >= 18446744073709551616.0 ? ~0ull : (uint64_t)scaled;
+    if (c > 0) c -= 1;
+    uint32_t ys[K], ts[KT];
+    // low 32 bits of c at limb offset s, high 32 bits at s + 1
+    shift_limbs(r1, s, ys);
+    (void)submul(r0, ys, (uint32_t)c);
+    shift_limbs(t1, s, ts);
+    addmul(t0, ts, (uint32_t)c);
+    if (c >> 32) {
+      shift_limbs(r1, s + 1, ys);
+      (void)submul(r0, ys, (uint32_t)(c >> 32));
+      shift_limbs(t1, s + 1, ts);
+      addmul(t0, ts, (uint32_t)(c >> 32));
+    }
   }
-  return fp_redc2(T, F);
 }
 
+// One point per lane, bound by integer and FP64 instructions.  Euclid's steps
+// are taken in groups on the leading bits (Lehmer): with u, v the two
+// remainders scaled to 48 bits, pairs of quotients come from u, v alone and
+// their product, a 2 x 2 matrix of factors below 2^26, is applied to the whole
+// numbers once.  A group's last pair must satisfy, for the factors y of r_1,
+//   w >= 4 y1,  v - w >= 4 (y1 + y0),  w - z >= 4 (y2 + y1),  z >= 4 y2 + B / 2^s + 4
+// (u, v, w, z successive remainders).  u and v are within 2 of the scaled
+// remainders (one truncation, and K 2^-53 of a value below 2^48), and a factor
+// of r_0 is no larger than that of r_1, so a remainder formed from them is
+// within 4 y of the scaled true one: the conditions make the true remainders
+// fall strictly in turn and stay above B, so the quotients are Euclid's own
+// (Collins' condition with room for the rounding) and the loop stops at the
+// same step.  What they do not settle takes a full_step.
+// A step on whole numbers at a time cost 2 K multiply-adds and two
+// conversions of K limbs per quotient: 468 us for 2^18 points with 14 primes;
+// the groups, limb counts that follow the number of primes, half-length
+// cofactors and Garner's digits from a table of weights take 89 us.
 template <int K>
 __global__ __launch_bounds__(256) void rr_kernel(RRArgs a) {
+  constexpr int KT = K / 2 + 1;
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= a.npts) return;
   const int P = a.nprimes;
   uint8_t st = 0;
-  // ---- residues and Garner's mixed-radix digits v_i (x = v_0 + p_0 (v_1 + p_1 (...)))
+  // ---- residues and Garner's mixed-radix digits v_i (x = v_0 + p_0 (v_1 + p_1 (...))):
+  // v_i = (r_i - sum_{j<i} v_j p_0 ... p_{j-1}) (p_0 ... p_{i-1})^-1 mod p_i
   uint32_t v[K];
 #pragma unroll
+  for (int i = 0; i < K; ++i) v[i] = i < P ? a.residues[(int64_t)i * a.ld + q] : 0u;
+#pragma unroll
   for (int i = 0; i < K; ++i) {
-    v[i] = 0;
     if (i < P) {
       const FpConst F = fpc(a.pc[i]);
-      const uint32_t r = a.residues[(int64_t)i * a.ld + q];
-      if (r >= (uint32_t)F.p) st = 2;
-      // X_{i-1} mod p_i by Horner over the digits found so far
-      int32_t t = 0;
-#pragma unroll
-      for (int j = i - 1; j >= 0; --j) {
-        const int32_t pj = mont_small(a.pc[j].p, F, a.pc[i].r2);
-        t = fp_add(fp_mul(t, pj, F), mont_small((int32_t)v[j], F, a.pc[i].r2), F);
+      if (v[i] >= (uint32_t)F.p) {
+        st = 2;
+        v[i] = 0;
       }
-      const int32_t rm = mont_small((int32_t)(r < (uint32_t)F.p ? r : 0u), F, a.pc[i].r2);
-      const int32_t d = fp_mul(fp_sub(rm, t, F), a.pc[i].minv, F);  // Montgomery form of v_i
-      v[i] = fp_to_canonical(fp_redc2((int64_t)d, F), F);
+      int64_t T = (int64_t)v[i];
+#pragma unroll
+      for (int j = 0; j < i; ++j) {
+        T = mad64((int32_t)v[j], a.w[i * (i - 1) / 2 + j], T);  // below 2^61 each
+        if (j & 1) T = fp_fold(T, F);
+      }
+      const int32_t d = fp_mul32(fp_redc1(fp_fold(T, F), F), a.pc[i].minv, F);  // in (-p, p)
+      v[i] = fp_to_canonical(d, F);
     }
   }
-  // ---- x = v_{P-1}; x = x p_i + v_i for i = P-2 .. 0
-  uint32_t x[K];
+  // ---- r_1 = x: x = v_{P-1}; x = x p_i + v_i for i = P-2 .. 0
+  uint32_t r0[K], r1[K], t0[KT], t1[KT];
 #pragma unroll
-  for (int k = 0; k < K; ++k) x[k] = 0;
+  for (int k = 0; k < K; ++k) r1[k] = 0;
 #pragma unroll
   for (int i = K - 1; i >= 0; --i) {
     if (i < P) {
       uint64_t carry = v[i];
       const uint32_t p = (uint32_t)a.pc[i].p;
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const uint64_t s = (uint64_t)x[k] * p + carry;
-        x[k] = (uint32_t)s;
+      for (int k = 0; k < K - i; ++k) {  // the product so far fills P - i limbs
+        const uint64_t s = (uint64_t)r1[k] * p + carry;
+        r1[k] = (uint32_t)s;
         carry = s >> 32;
       }
     }
   }
   // ---- extended Euclid on (M, x) until the remainder is <= B
-  uint32_t r0[K], r1[K], t0[K], t1[K], Bv[K];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    r0[k] = a.M[k];
-    r1[k] = x[k];
+  for (int k = 0; k < K; ++k) r0[k] = a.M[k];
+#pragma unroll
+  for (int k = 0; k < KT; ++k) {
     t0[k] = 0;
     t1[k] = k == 0 ? 1u : 0u;
-    Bv[k] = a.B[k];
   }
-  // every step shrinks the remainders: a small quotient step at least halves
-  // r_j two steps on, a large-quotient piece removes 32 bits or more; the cap
-  // only guarantees that every lane leaves the loop
+  bool neg = false;  // the sign of t_1
+  // every step shrinks the remainders: a quotient at least halves r_j two
+  // steps on, a large-quotient piece removes 32 bits or more; the cap only
+  // guarantees that every lane leaves the loop
   const int cap = 96 * K + 64;
   int it = 0;
-  while (cmp(r1, Bv) > 0 && it < cap) {
-    ++it;
-    const double qe = to_double(r0) / to_double(r1);
-    if (qe < 2147483648.0) {
-      uint32_t qq = (uint32_t)qe;
-      int64_t bo = submul(r0, r1, qq);
-      while (bo < 0) {  // over-estimate: add r1 back
-        uint64_t carry = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const uint64_t s = (uint64_t)r0[k] + r1[k] + carry;
-          r0[k] = (uint32_t)s;
-          carry = s >> 32;
-        }
-        bo += (int64_t)carry;
-        --qq;
-      }
-      while (cmp(r0, r1) >= 0) {  // under-estimate
-        sub_from(r0, r1);
-        ++qq;
-      }
-      (void)submul(t0, t1, qq);
-      // (r0, r1) <- (r1, r0 - q r1), (t0, t1) <- (t1, t0 - q t1)
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const uint32_t a0 = r0[k];
-        r0[k] = r1[k];
-        r1[k] = a0;
-        const uint32_t b0 = t0[k];
-        t0[k] = t1[k];
-        t1[k] = b0;
-      }
+  for (; it < cap; ++it) {
+    const double r0d = to_double(r0), r1d = to_double(r1);
+    // clearly above B, else compare the limbs
+    if (!(r1d > a.B_double * (1.0 + 0x1p-40)) && not_above<K, KT>(r1, a.B)) break;
+    int e = __builtin_amdgcn_frexp_exp(r0d) - 48;
+    e = e > 0 ? e : 0;
+    double u = __builtin_trunc(__builtin_amdgcn_ldexp(r0d, -e)), v1 = __builtin_trunc(__builtin_amdgcn_ldexp(r1d, -e));
+    const double stop = __builtin_amdgcn_ldexp(a.B_double, -e) + 4.0;
+    double ma = 1.0, mb = 0.0, mc = 0.0, md = 1.0;  // u = ma r_0 - mb r_1, v1 = md r_1 - mc r_0
+    bool some = false;
+    for (;;) {
+      // the estimates may be off by one for a large quotient: the conditions
+      // then fail, as they do for v1 = 0 or w = 0 (a NaN compares false)
+      const double q1 = __builtin_trunc(u * __builtin_amdgcn_rcp(v1));
+      const double w = __builtin_fma(-q1, v1, u);
+      const double q2 = __builtin_trunc(v1 * __builtin_amdgcn_rcp(w));
+      const double z = __builtin_fma(-q2, w, v1);
+      const double y1 = __builtin_fma(q1, md, mb), y2 = __builtin_fma(q2, y1, md);
+      const bool ok = (w >= 4.0 * y1) & (v1 - w >= 4.0 * (y1 + md)) & (w - z >= 4.0 * (y2 + y1)) &
+                      (z >= __builtin_fma(4.0, y2, stop));
+      if (!ok) break;
+      const double x1 = __builtin_fma(q1, mc, ma);
+      mc = __builtin_fma(q2, x1, mc);
+      ma = x1;
+      mb = y1;
+      md = y2;
+      u = w;
+      v1 = z;
+      some = true;
+    }
+    if (some) {
+      const uint32_t A = (uint32_t)ma, Bm = (uint32_t)mb, C = (uint32_t)mc, D = (uint32_t)md;
+      mix_sub(r0, r1, A, Bm, C, D);
+      mix_add(t0, t1, A, Bm, C, D);
     } else {
-      // take c 2^(32 s) out of the quotient, c < 2^64 an under-estimate
-      int e = 0;
-      (void)frexp(qe, &e);  // qe in [2^(e-1), 2^e)
-      const int s = e > 64 ? (e - 64 + 31) / 32 : 0;
-      const double scaled = ldexp(qe, -32 * s) * (1.0 - 0x1p-40);
-      uint64_t c = scaled >= 18446744073709551616.0 ? ~0ull : (uint64_t)scaled;
-      if (c > 0) c -= 1;
-      uint32_t ys[K], ts[K];
-      // low 32 bits of c at limb offset s, high 32 bits at s + 1
-      shift_limbs(r1, s, ys);
-      (void)submul(r0, ys, (uint32_t)c);
-      shift_limbs(t1, s, ts);
-      (void)submul(t0, ts, (uint32_t)c);
-      if (c >> 32) {
-        shift_limbs(r1, s + 1, ys);
-        (void)submul(r0, ys, (uint32_t)(c >> 32));
-        shift_limbs(t1, s + 1, ts);
-        (void)submul(t0, ts, (uint32_t)(c >> 32));
-      }
+      full_step<K, KT>(r0, r1, t0, t1, neg, r0d / r1d);
     }
   }
   // ---- checks and output: a = sign(t) r, b = |t|
-  const bool neg = (t1[K - 1] >> 31) != 0;
-  if (neg) negate(t1);
-  bool ok = st == 0 && it < cap && !is_zero(t1) && cmp(t1, Bv) <= 0;
+  uint32_t any = 0;
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    if (i < P) {
-      const FpConst F = fpc(a.pc[i]);
-      const int32_t c32m = fp_mul(a.pc[i].c32, a.pc[i].r2, F);  // 2^32 R mod p
-      if (mod_prime(t1, F, c32m) == 0) ok = false;              // gcd(t, M) != 1
-    }
-  }
+  for (int k = 0; k < KT; ++k) any |= t1[k];
+  bool ok = st == 0 && it < cap && any != 0 && not_above<KT, KT>(t1, a.B);
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+    if (i < P && divisible(t1, fpc(a.pc[i]))) ok = false;  // gcd(t, M) != 1
   if (ok && neg) negate(r1);
   const int L = a.L;
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
+  for (int k = 0; k < KT; ++k) {
     if (k < L) {
-      a.num[(int64_t)k * a.ld + q] = ok ? (int32_t)r1[k] : 0;
+      a.num[(int64_t)k * a.ld + q] = ok ? (int32_t)(k < K ? r1[k] : 0u) : 0;
       a.den[(int64_t)k * a.ld + q] = ok ? t1[k] : 0u;
     }
   }
@@ -540,16 +637,15 @@ int bg_rational_reconstruct(int nprimes, const uint32_t* primes, int64_t npts, i
     const bg::FpConst k = bg::make_fp_const((uint32_t)p);
     bg::PrimeConst& c = a.pc[i];
     c.p = k.p;
-    c.h = k.h;
     c.c32 = k.c32;
-    c.c64 = k.c64;
     c.pinv = k.pinv;
-    const uint64_t R = bg::powmod64(2, 64, p);
-    c.r2 = bg::bal((unsigned __int128)R * R % p, p);
-    uint64_t prod = 1;  // p_0 ... p_{i-1} mod p_i
-    for (int j = 0; j < i; ++j) prod = (unsigned __int128)prod * (primes[j] % p) % p;
+    uint64_t prod = 1;  // p_0 ... p_{j-1} mod p_i
+    for (int j = 0; j < i; ++j) {
+      a.w[i * (i - 1) / 2 + j] = -bg::bal(prod, p);
+      prod = (unsigned __int128)prod * (primes[j] % p) % p;
+    }
     const uint64_t inv = bg::powmod64(prod, p - 2, p);
-    c.minv = bg::bal((unsigned __int128)inv * R % p, p);
+    c.minv = bg::bal((unsigned __int128)inv * bg::powmod64(2, 64, p) % p, p);
     bg::big_mul_small(M, (uint32_t)p);
   }
   bg::Big Mm1 = M;  // (M - 1) / 2; M is odd, so M - 1 only clears bit 0
@@ -557,12 +653,20 @@ int bg_rational_reconstruct(int nprimes, const uint32_t* primes, int64_t npts, i
   for (size_t k = 0; k < Mm1.size(); ++k) Mm1[k] = (Mm1[k] >> 1) | (k + 1 < Mm1.size() ? (Mm1[k + 1] << 31) : 0u);
   const bg::Big Bv = bg::big_isqrt(Mm1);
   for (size_t k = 0; k < M.size() && k < (size_t)BG_RR_MAX_PRIMES; ++k) a.M[k] = M[k];
-  for (size_t k = 0; k < Bv.size() && k < (size_t)BG_RR_MAX_PRIMES; ++k) a.B[k] = Bv[k];
+  for (size_t k = Bv.size(); k-- > 0;) {
+    if (k < sizeof(a.B) / sizeof(a.B[0])) a.B[k] = Bv[k];
+    a.B_double = a.B_double * 4294967296.0 + (double)Bv[k];
+  }
   const int64_t blocks = (npts + 255) / 256;
   if (blocks > 0x7FFFFFFF) return BG_EINVAL;
-  const void* fn = nprimes <= 8    ? reinterpret_cast<const void*>(&bg::rr_kernel<8>)
-                   : nprimes <= 16 ? reinterpret_cast<const void*>(&bg::rr_kernel<16>)
-                                   : reinterpret_cast<const void*>(&bg::rr_kernel<32>);
+  static const void* const kernels[] = {
+      reinterpret_cast<const void*>(&bg::rr_kernel<2>),  reinterpret_cast<const void*>(&bg::rr_kernel<4>),
+      reinterpret_cast<const void*>(&bg::rr_kernel<6>),  reinterpret_cast<const void*>(&bg::rr_kernel<8>),
+      reinterpret_cast<const void*>(&bg::rr_kernel<10>), reinterpret_cast<const void*>(&bg::rr_kernel<12>),
+      reinterpret_cast<const void*>(&bg::rr_kernel<14>), reinterpret_cast<const void*>(&bg::rr_kernel<16>),
+      reinterpret_cast<const void*>(&bg::rr_kernel<20>), reinterpret_cast<const void*>(&bg::rr_kernel<24>),
+      reinterpret_cast<const void*>(&bg::rr_kernel<28>), reinterpret_cast<const void*>(&bg::rr_kernel<32>)};
+  const void* fn = kernels[nprimes <= 16 ? (nprimes - 1) / 2 : 8 + (nprimes - 17) / 4];
   void* args[] = {&a};
   return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256), args, 0, static_cast<hipStream_t>(hip_stream)) ==
                  hipSuccess
