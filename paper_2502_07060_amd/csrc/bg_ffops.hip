@@ -5,23 +5,19 @@
 // fastest one in every array (element e of event q at e * ld + q), as in the
 // amplitude entry points, so the lanes of a wave read consecutive words.
 //
-// Contraction, one event per lane: z[i][k] = sum_j x[i][j] y[j][k].  Values
+// Contraction, one event per lane: z[i][k] = sum_j x[i][j] y[j][k] as a sum of
+// outer products, a tile of TI x TK outputs in registers (below).  Values
 // are taken as balanced representatives (|v| <= (p-1)/2), so a product is
 // below 2^60 and four of them fit beside a folded accumulator (field_fp.h);
-// each output is reduced once at the end (REDC2 and one product with R^2).
-// Outputs are computed eight columns k at a time, so every x[i][j] is read
-// once per eight outputs; repeated reads of an event's operands hit the
-// caches (the algorithmic traffic is read once).
+// each output is reduced once at the end.
 //
 // Division: Montgomery batch inversion over 16 values per lane (one Fermat
 // power per 16 quotients).
-//
-// Small contractions (J, K <= 8) have a kernel of their own that reads y once
-// per event into registers (static 8 x 8 slots, guarded by the run-time
-// sizes) and each x[i][j] once.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
+
+#include <utility>
 
 #include "bg.h"
 #include "bg_registry.h"
@@ -30,7 +26,7 @@
 namespace bg {
 namespace {
 
-constexpr int kKBlock = 8;
+constexpr int kTile = 8;  // largest tile side
 constexpr int kDivChunk = 16;
 
 struct ContractArgs {
@@ -40,101 +36,135 @@ struct ContractArgs {
   uint8_t* status;
   int64_t npts, ld;
   int I, J, K;
-  int y_batched;
   FpConst fp;
-  int32_t r2;  // R^2 mod p, balanced
 };
 
-__device__ __forceinline__ int32_t bal_of(uint32_t v, const FpConst& F, uint32_t& maxraw) {
-  maxraw = maxraw > v ? maxraw : v;
-  return fp_from_canonical(v < (uint32_t)F.p ? v : 0u, F);
-}
-
+// A tile of outputs per lane: TI x TK int64 accumulators; each step of j loads
+// TI values of x and TK of y and adds their products, so an event's inputs are
+// read once when I, K <= 8 (ceil(K / TK) and ceil(I / TI) times otherwise,
+// mostly from cache).  Bound by HBM traffic: the loads of the next two j are
+// issued before the products of the current two, without conditions on values,
+// so a wave keeps 2 (TI + TK) loads in flight.  The tile sides are compile-time
+// (no guards inside); they split I and K evenly into tiles of at most 8, the
+// last tile repeating its last row or column where they do not divide.
+// Before, y lay in an 8 x 8 array behind run-time guards for J, K <= 8 (each
+// load waited for in a block of its own), and larger J or K read y once per
+// row of x after a pass over all inputs for the status.  Events by I x J x K,
+// before and now: 2^20 of 6x6x6 247 -> 100 us (4.5 TB/s, a large copy
+// reaches 4.9); 150001 of 6x36x6 660 -> 72 us.
+//
+// YB: y per event; else one y for all events, read through scalar loads.
+template <int TI, int TK, bool YB>
 __global__ __launch_bounds__(256) void contract_kernel(ContractArgs a) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= a.npts) return;
   const FpConst& F = a.fp;
-  const int64_t ys = a.y_batched ? a.ld : 1;   // element stride of y ([J][K][ld] or [J][K])
-  const int64_t yq = a.y_batched ? q : 0;
+  const uint32_t* const xq = a.x + q;
+  const uint32_t* const yq = YB ? a.y + q : a.y;
+  const int64_t ys = YB ? a.ld : 1;  // element stride of y ([J][K][ld] or [J][K])
+  const bool one_tile = a.I <= TI && a.K <= TK;
   uint32_t maxraw = 0;
-  // a pass over the inputs finds non-canonical residues first, so that the
-  // outputs of such an event are all sentinels
-  for (int e = 0; e < a.I * a.J; ++e) maxraw = max(maxraw, a.x[(int64_t)e * a.ld + q]);
-  for (int e = 0; e < a.J * a.K; ++e) maxraw = max(maxraw, a.y[(int64_t)e * ys + yq]);
-  const bool bad = maxraw >= (uint32_t)F.p;
-  for (int i = 0; i < a.I; ++i) {
-    for (int k0 = 0; k0 < a.K; k0 += kKBlock) {
-      int64_t acc[kKBlock];
+  for (int i0 = 0; i0 < a.I; i0 += TI) {
+    for (int k0 = 0; k0 < a.K; k0 += TK) {
+      int64_t acc[TI][TK];
 #pragma unroll
-      for (int u = 0; u < kKBlock; ++u) acc[u] = 0;
-      uint32_t dummy = 0;
-      int j = 0;
-      for (; j < a.J; ++j) {
-        const int32_t xv = bal_of(a.x[((int64_t)i * a.J + j) * a.ld + q], F, dummy);
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int u = 0; u < kKBlock; ++u) {
-          if (k0 + u < a.K) {
-            const int32_t yv = bal_of(a.y[((int64_t)j * a.K + k0 + u) * ys + yq], F, dummy);
-            acc[u] = mad64(xv, yv, acc[u]);
+        for (int k = 0; k < TK; ++k) acc[i][k] = 0;
+      uint32_t xn[2][TI], yn[2][TK];
+      const auto load = [&](int j0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          if (j0 + u < a.J) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+              const int ii = i0 + i < a.I ? i0 + i : a.I - 1;
+              xn[u][i] = xq[((int64_t)ii * a.J + j0 + u) * a.ld];
+            }
+#pragma unroll
+            for (int k = 0; k < TK; ++k) {
+              const int kk = k0 + k < a.K ? k0 + k : a.K - 1;
+              yn[u][k] = yq[((int64_t)(j0 + u) * a.K + kk) * ys];
+            }
+          } else {
+#pragma unroll
+            for (int i = 0; i < TI; ++i) xn[u][i] = 0;
+#pragma unroll
+            for (int k = 0; k < TK; ++k) yn[u][k] = 0;
           }
         }
-        if ((j & 3) == 3) {  // four products of < 2^60 beside a folded accumulator
+      };
+      load(0);
+      for (int j0 = 0; j0 < a.J; j0 += 2) {
+        uint32_t xc[2][TI], yc[2][TK];
 #pragma unroll
-          for (int u = 0; u < kKBlock; ++u) acc[u] = fp_fold(acc[u], F);
+        for (int u = 0; u < 2; ++u) {
+#pragma unroll
+          for (int i = 0; i < TI; ++i) xc[u][i] = xn[u][i];
+#pragma unroll
+          for (int k = 0; k < TK; ++k) yc[u][k] = yn[u][k];
+        }
+        if (j0 + 2 < a.J) load(j0 + 2);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          // a value >= p is taken as it is (its event's outputs are replaced
+          // by the sentinel, whatever its products were)
+          int32_t yv[TK];
+#pragma unroll
+          for (int k = 0; k < TK; ++k) {
+            maxraw = max(maxraw, yc[u][k]);
+            yv[k] = fp_from_canonical(yc[u][k], F);
+          }
+#pragma unroll
+          for (int i = 0; i < TI; ++i) {
+            maxraw = max(maxraw, xc[u][i]);
+            const int32_t xv = fp_from_canonical(xc[u][i], F);
+#pragma unroll
+            for (int k = 0; k < TK; ++k) acc[i][k] = mad64(xv, yv[k], acc[i][k]);
+          }
+        }
+        if (j0 & 2) {  // four products of < 2^60 beside a folded accumulator
+#pragma unroll
+          for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int k = 0; k < TK; ++k) acc[i][k] = fp_fold(acc[i][k], F);
         }
       }
+      // sum 2^-32 2^64 2^-32, in (-p, p); with more than one tile an event that
+      // turns out to hold a non-canonical input is overwritten at the end
+      const bool bad = one_tile && maxraw >= (uint32_t)F.p;
 #pragma unroll
-      for (int u = 0; u < kKBlock; ++u) {
-        if (k0 + u < a.K) {
-          const int32_t s = fp_mul(fp_redc2(fp_fold(acc[u], F), F), a.r2, F);  // sum R^-1 R^2 R^-1
-          a.z[((int64_t)i * a.K + k0 + u) * a.ld + q] = bad ? 0xFFFFFFFFu : fp_to_canonical(s, F);
+      for (int i = 0; i < TI; ++i) {
+        if (i0 + i < a.I) {
+#pragma unroll
+          for (int k = 0; k < TK; ++k) {
+            if (k0 + k < a.K) {
+              const int32_t s = fp_mul32(fp_redc1(fp_fold(acc[i][k], F), F), F.c64, F);
+              a.z[((int64_t)(i0 + i) * a.K + k0 + k) * a.ld + q] = bad ? 0xFFFFFFFFu : fp_to_canonical(s, F);
+            }
+          }
         }
-      }
-    }
-  }
-  if (a.status) a.status[q] = bad ? PT_BADRESIDUE : PT_OK;
-}
-
-// J, K <= kSmall: y in registers, every input read once
-constexpr int kSmall = 8;
-
-__global__ __launch_bounds__(256) void contract_small_kernel(ContractArgs a) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q >= a.npts) return;
-  const FpConst& F = a.fp;
-  const int64_t ys = a.y_batched ? a.ld : 1;
-  const int64_t yq = a.y_batched ? q : 0;
-  uint32_t maxraw = 0;
-  int32_t yv[kSmall][kSmall];
-#pragma unroll
-  for (int j = 0; j < kSmall; ++j)
-#pragma unroll
-    for (int k = 0; k < kSmall; ++k)
-      yv[j][k] = (j < a.J && k < a.K) ? bal_of(a.y[((int64_t)j * a.K + k) * ys + yq], F, maxraw) : 0;
-  // outputs go out as they are made; an event with a non-canonical input is
-  // overwritten with sentinels afterwards
-  for (int i = 0; i < a.I; ++i) {
-    int32_t xv[kSmall];
-#pragma unroll
-    for (int j = 0; j < kSmall; ++j) xv[j] = j < a.J ? bal_of(a.x[((int64_t)i * a.J + j) * a.ld + q], F, maxraw) : 0;
-#pragma unroll
-    for (int k = 0; k < kSmall; ++k) {
-      if (k < a.K) {
-        int64_t acc = 0;
-#pragma unroll
-        for (int j = 0; j < kSmall; ++j) {
-          acc = mad64(xv[j], yv[j][k], acc);  // zero slots add nothing
-          if (j == 3) acc = fp_fold(acc, F);
-        }
-        const int32_t s = fp_mul(fp_redc2(fp_fold(acc, F), F), a.r2, F);
-        a.z[((int64_t)i * a.K + k) * a.ld + q] = fp_to_canonical(s, F);
       }
     }
   }
   const bool bad = maxraw >= (uint32_t)F.p;
-  if (bad)
+  if (bad && !one_tile)
     for (int e = 0; e < a.I * a.K; ++e) a.z[(int64_t)e * a.ld + q] = 0xFFFFFFFFu;
   if (a.status) a.status[q] = bad ? PT_BADRESIDUE : PT_OK;
+}
+
+// the kernel of a tile shape: index ((TI - 1) kTile + TK - 1) 2 + YB
+template <int... Is>
+const void* contract_table(int at, std::integer_sequence<int, Is...>) {
+  static const void* const fn[] = {
+      reinterpret_cast<const void*>(&contract_kernel<Is / 2 / kTile + 1, Is / 2 % kTile + 1, (Is & 1) != 0>)...};
+  return fn[at];
+}
+
+// side of the tiles that split n evenly into tiles of at most kTile
+int tile_side(int n) {
+  const int tiles = (n + kTile - 1) / kTile;
+  return (n + tiles - 1) / tiles;
 }
 
 struct DivideArgs {
@@ -228,16 +258,17 @@ int bg_fp_contract(uint32_t p, int I, int J, int K, int64_t npts, int64_t ld, co
   a.I = I;
   a.J = J;
   a.K = K;
-  a.y_batched = y_batched ? 1 : 0;
   a.fp = bg::make_fp_const(p);
-  a.r2 = bg::r2_of(p);
-  const int64_t blocks = (npts + 255) / 256;
+  // one wave a block: few events still reach every CU (blocks of 256 lanes are
+  // no faster at 2^20 events: 100 us both)
+  const int block = 64;
+  const int64_t blocks = (npts + block - 1) / block;
   if (blocks > 0x7FFFFFFF) return BG_EINVAL;
   void* args[] = {&a};
-  const void* fn = (J <= bg::kSmall && K <= bg::kSmall) ? reinterpret_cast<const void*>(&bg::contract_small_kernel)
-                                                        : reinterpret_cast<const void*>(&bg::contract_kernel);
-  return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256),
-                         args, 0, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+  const int at = ((bg::tile_side(I) - 1) * bg::kTile + bg::tile_side(K) - 1) * 2 + (y_batched ? 1 : 0);
+  const void* fn = bg::contract_table(at, std::make_integer_sequence<int, 2 * bg::kTile * bg::kTile>{});
+  return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3((unsigned)block), args, 0,
+                         static_cast<hipStream_t>(hip_stream)) == hipSuccess
              ? BG_OK
              : BG_EHIP;
 }

@@ -43,3 +43,35 @@ def test_from_rational_layout(torch_dev, p, count, skip):
         assert int(o[o0 + e]) == want, e
     assert (o[:o0] == 7).all() and (o[o0 + count:] == 7).all()   # nothing past the ends
     assert (s[:s0] == 7).all() and (s[s0 + count:] == 7).all()
+
+
+@pytest.mark.parametrize("batched", [True, False])
+@pytest.mark.parametrize("Id,J,K,n", [(8, 4, 8, 63), (9, 5, 7, 64), (7, 2, 9, 65), (16, 3, 17, 70), (17, 1, 16, 5), (6, 36, 6, 129),
+                                      (1, 37, 8, 66), (8, 6, 1, 1), (2, 3, 2, 65535), (3, 2, 1, 65537)])
+def test_contract_tiles(torch_dev, Id, J, K, n, batched):
+    torch, dev = torch_dev
+    p = 998244353 if (Id + J) % 2 else 2147483647
+    rng = np.random.default_rng(Id * 100 + J * 10 + K)
+    ld = n + 3
+    x = rng.integers(0, p, size=(Id, J, ld))
+    y = rng.integers(0, p, size=(J, K, ld) if batched else (J, K))
+    x[:, :, 0] = p - 1                     # the largest sums of one sign
+    bad = np.zeros(n, bool)
+    if n > 4:
+        x[Id - 1, J - 1, n - 1] = 0xFFFFFFFF   # in the last tile: outputs of the first ones are replaced too
+        bad[n - 1] = True
+        if batched:
+            y[J - 1, K - 1, 2] = p
+            bad[2] = True
+    if batched:
+        y[:, :, 0] = p - 1
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a.astype(np.uint32)).view(np.int32)).to(dev)
+    z, st = bg.bg_fp_contract(p, up(x), up(y), y_batched=batched, npts=n)
+    torch.cuda.synchronize()
+    want = np.zeros((Id, K, n), np.int64)
+    for j in range(J):                     # products below 2^62, reduced one by one
+        yj = y[j][:, :n] if batched else y[j][:, None]
+        want = (want + x[:, j, None, :n] % p * (yj[None] % p) % p) % p
+    want[:, :, bad] = SENTINEL
+    assert np.array_equal(u32(z)[:, :, :n], want)
+    assert np.array_equal(st.cpu().numpy(), np.where(bad, 2, 0))
