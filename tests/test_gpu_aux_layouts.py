@@ -75,3 +75,30 @@ def test_contract_tiles(torch_dev, Id, J, K, n, batched):
     want[:, :, bad] = SENTINEL
     assert np.array_equal(u32(z)[:, :, :n], want)
     assert np.array_equal(st.cpu().numpy(), np.where(bad, 2, 0))
+
+
+@pytest.mark.parametrize("p", [3, 1009, 1073741827, 2147483647])
+@pytest.mark.parametrize("count,skip", [(1, 0), (1023, 0), (1025, 0), (4095, 0), (4096, 0), (4097, 0), (4096, 1), (9001, 3)])
+def test_divide_layout(torch_dev, p, count, skip):
+    torch, dev = torch_dev
+    rng = np.random.default_rng(count + skip + p % 89)
+    x, y = rng.integers(0, p, size=count), rng.integers(1, p, size=count)
+    x[-1], y[-1] = p - 1, p - 1
+    y[count // 2] = 0
+    if count > 8:
+        x[count // 3], y[count // 4] = p, 0xFFFFFFFF
+        x[count // 5], y[count // 5] = p + 1, 0     # a bad residue wins over the zero divisor
+    shift = lambda a: torch.from_numpy(np.concatenate([np.zeros(skip, np.uint32), a.astype(np.uint32)]).view(np.int32)).to(dev)[skip:]
+    bad, zero = (x >= p) | (y >= p), y == 0
+    table = {}
+    inv = np.array([table.setdefault(int(b), pow(int(b), -1, p)) if not (s or t) else 0 for b, s, t in zip(y, bad, zero)])
+    want = np.where(bad | zero, SENTINEL, x % p * inv % p)
+    z, st = bg.bg_fp_divide(p, shift(x), shift(y))
+    torch.cuda.synchronize()
+    assert np.array_equal(u32(z), want)
+    assert np.array_equal(st.cpu().numpy(), np.where(bad, 2, np.where(zero, 1, 0)))
+    d = p - 1 if count % 2 else p // 2
+    z, st = bg.bg_fp_divide(p, shift(x), d)
+    torch.cuda.synchronize()
+    assert np.array_equal(u32(z), np.where(x >= p, SENTINEL, x % p * pow(d, -1, p) % p))
+    assert np.array_equal(st.cpu().numpy(), np.where(x >= p, 2, 0))
