@@ -4,6 +4,8 @@ small primes, value by value against Python integers."""
 import numpy as np
 import pytest
 
+from oracle import fields
+from oracle import states as S
 from paper_2502_07060_amd import bg
 from paper_2502_07060_amd import inputs as I
 
@@ -102,3 +104,33 @@ def test_divide_layout(torch_dev, p, count, skip):
     torch.cuda.synchronize()
     assert np.array_equal(u32(z), np.where(x >= p, SENTINEL, x % p * pow(d, -1, p) % p))
     assert np.array_equal(st.cpu().numpy(), np.where(x >= p, 2, 0))
+
+
+@pytest.mark.parametrize("d", [4, 5, 6, 7, 8, 9, 10])
+@pytest.mark.parametrize("p", [5, 13, 1009, 998244353, P])
+def test_states_small_fields(torch_dev, d, p):
+    """Small primes, where every denominator vanishes at some points and both
+    spinor charts occur, against the oracle (statuses and residues)."""
+    torch, dev = torch_dev
+    n, ld = 300 if p < 1000 else 70, 301
+    rng = np.random.default_rng(d * 10 + p % 7)
+    k = I.fp_null(rng, p, (ld,), d) if p > 5 else rng.integers(0, p, size=(ld, d))   # not massless: the formulas hold
+    chi = I.fp_null(rng, p, (ld,), 4)
+    k[1, 3] = (p - k[1, 0]) % p            # k+ = 0
+    chi[2] = [p - 1, 0, 0, 1]              # chi+ = 0
+    k[3, 0] = p                            # not canonical
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a.T.astype(np.uint32)).view(np.int32)).to(dev)
+    e, t, st = bg.bg_states_fp(up(k), up(chi), p, npts=n)
+    torch.cuda.synchronize()
+    e, t, st = u32(e), u32(t), st.cpu().numpy()
+    F, ip = fields.Fp(p), I.fp_sqrt_minus_one(p)
+    for q in range(n):
+        if (k[q] >= p).any():
+            assert st[q] == 2 and (e[:, :, q] == SENTINEL).all() and (t[:, :, q] == SENTINEL).all()
+            continue
+        s, E, T = S.states(F, [int(x) for x in k[q]], [int(x) for x in chi[q]], ip)
+        assert st[q] == s, q
+        if s == 0:
+            assert np.array_equal(e[:, :, q], np.array(E)) and np.array_equal(t[:, :, q], np.array(T)), q
+        else:
+            assert (e[:, :, q] == SENTINEL).all() and (t[:, :, q] == SENTINEL).all()
