@@ -50,6 +50,11 @@
  * asynchronous on the given HIP stream (NULL = the default stream): results
  * are valid once the stream has been synchronised.  npts == 0 is a no-op.
  * The compute entry points allocate no device memory and are thread safe.
+ *
+ * Kernels.  A call runs the kernel pinned for its (field, n, d) (see
+ * bg_select_variant), else a default for (field, n, d, npts): few points take
+ * more lanes each.  Over Z_p every kernel gives the same residues; over C two
+ * kernels differ by rounding, so results are bit-identical for equal npts.
  */
 #ifndef BG_MI355X_H
 #define BG_MI355X_H
@@ -309,7 +314,7 @@ int bg_fp_divide_scalar(uint32_t p, int64_t count, const uint32_t* x, uint32_t y
  * precompiled kernels for many (n, d) at once.  Each group has the
  * layout and meaning of one bg_amplitudes_* call; every group is validated
  * before anything is enqueued (the first invalid group's error is returned).
- * Groups run the kernel variant selected for their (field, n, d), longest
+ * Groups run the kernel a single call of their size would run, longest
  * first, spread over internal streams that fork from and join back to
  * hip_stream: results are valid once hip_stream has been synchronised.
  * Groups must not overlap in their outputs.
@@ -328,9 +333,10 @@ typedef struct {
 int bg_batch_run(const bg_group* groups, int ngroups, void* hip_stream);
 
 /*
- * The same call with options.  BG_BATCH_QUEUE: every group whose selected
- * kernel is a lane-group (runtime-n) kernel is served by one persistent launch
- * per such kernel variant instead of one launch per group.  Its blocks stay
+ * The same call with options.  BG_BATCH_QUEUE: every group whose (field, n, d)
+ * has no register kernel, or is pinned to a lane-group (runtime-n) kernel, is
+ * served by one persistent launch per such kernel variant instead of one launch
+ * per group.  Its blocks stay
  * resident and take (group, point range) tiles from a device work queue, the
  * groups ordered by work per point, longest first; register-kernel groups run
  * as in bg_batch_run.  The queue's counters and group table (about 160 bytes
@@ -347,7 +353,7 @@ int bg_batch_run_ex(const bg_group* groups, int ngroups, int flags, void* hip_st
  * For callers that cannot allocate device memory (code under graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): bg_batch_run_ex with
  * BG_BATCH_QUEUE, but the queue lives in a fixed device array of the library
- * (256 KiB per GPU, held until the process ends; enough for about 1500
+ * (264 KiB per GPU, held until the process ends; enough for about 1500
  * lane-group groups per call) and every launch goes to hip_stream in turn,
  * so the call allocates nothing, creates no streams and calls no allocating
  * routine.  The array keeps the previous call's contents; each call rewrites
@@ -360,7 +366,7 @@ int bg_batch_run_noalloc(const bg_group* groups, int ngroups, void* hip_stream);
 
 /*
  * A batch plan records the launches of a fixed set of groups (pointers and
- * sizes fixed, kernel variants as selected at creation) as one hipGraph of
+ * sizes fixed, kernels as single calls would run at creation) as one hipGraph of
  * independent kernel nodes; bg_batch_plan_launch replays it on hip_stream with
  * a single graph launch.  Plans own no device memory (but see
  * bg_batch_plan_create_ex).
@@ -390,12 +396,12 @@ int bg_batch_plan_destroy(bg_batch_plan* plan);
  * runs (s = 16 complex, 4 F_p; columns padded to 64 points, parts to 256
  * bytes).  Requests are admitted first come, first served as arena space
  * and launch slots free up; requests waiting for the same (field, n, d, p)
- * are merged into one kernel launch over adjacent columns; several launches
+ * (over C also of the same kernel) are merged into one kernel launch over
+ * adjacent columns; several launches
  * are in flight at once on separate streams, their copies overlapping other
  * launches' kernels.  Every point is computed exactly as by
- * bg_amplitudes_c128 / bg_amplitudes_fp with the kernel variant selected
- * for its (field, n, d), so a request's results do not depend on what it
- * was batched with.
+ * bg_amplitudes_c128 / bg_amplitudes_fp computes it in a call of the request's
+ * own size, so a request's results do not depend on what it was batched with.
  *
  * With flags = BG_SERVER_PLAIN the server runs one request per launch, one at
  * a time, in arrival order, on one stream (the plain baseline).
@@ -462,7 +468,8 @@ typedef struct {
   int padded;           /* lanes > 1 runtime-n kernel whose LDS table rows are
                            padded to an odd number of 16-byte units            */
   int max_d;            /* largest d the kernel handles                        */
-  int selected;         /* 1 if this variant is the one currently in use        */
+  int selected;         /* 1 if this variant is pinned or, without a pin, the
+                           default for many points                              */
 } bg_variant_info;
 
 /* Fills up to cap entries for (field, n, d); returns the number available

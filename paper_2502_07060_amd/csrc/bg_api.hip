@@ -97,16 +97,6 @@ int32_t fp_sqrt_minus_one_mont(uint32_t p) {
 // ---------------------------------------------------------------------------
 // variant choice
 // ---------------------------------------------------------------------------
-// Default lanes per point, from timings on gfx950 at n = 8 (F_p d = 6: two
-// lanes 0.70 ms vs one lane 0.80 ms per 2^20 points; complex d = 4: two lanes
-// 0.92 ms vs four 1.10 ms); bg_autotune measures the rest.
-static int preferred_lanes(int field, int N, int d) {
-  (void)field;
-  (void)N;
-  (void)d;
-  return 2;
-}
-
 static bool fits(const Variant& v, int field, int n, int d) {
   if (v.field != field) return false;
   if (v.generic) return v.DL >= d;
@@ -149,58 +139,170 @@ int select_variant(int metric, int field, int n, int d, int index) {
   return BG_OK;
 }
 
-const Variant* default_variant(int field, int n, int d);
-
-// a wide kernel keeps at least 512 lanes (8 waves) busy per CU at this N
-static bool best_fills(const Variant* v, int N) {
-  const unsigned per = v->lds_per_point ? v->lds_per_point(N) : 0;
-  return per && (long)(max_lds_per_block() / per) * v->L >= 512;
+// the register kernel of (field, n) with L lanes per point and the fewest
+// components per lane that cover d (null if none is compiled)
+static const Variant* register_variant(int field, int n, int d, int L) {
+  const Variant* best = nullptr;
+  for (const Variant& v : registry()) {
+    if (v.generic || v.field != field || v.N != n - 1 || v.L != L || v.DL * L < d) continue;
+    if (!best || v.DL < best->DL || (v.DL == best->DL && v.lds_tables && !best->lds_tables)) best = &v;
+  }
+  return best;
 }
 
-const Variant* choose_variant(int field, int n, int d) {
+// the lane-group kernel of G work items on LC lanes each (null if not compiled)
+static const Variant* lane_group_variant(int field, int dmax, int G, int LC, bool padded) {
+  for (const Variant& v : registry())
+    if (v.generic && v.field == field && v.DL == dmax && v.L == G * LC && v.L > 1 && v.split == LC && v.padded == padded)
+      return &v;
+  return nullptr;
+}
+
+// Kernel choice without a pin, by (field, n, d) and the number of points.
+// Measured on gfx950 with every compiled kernel at n = 4..14, d = 4..10 and 300
+// to 2^19 points; figures are us per launch, this choice against the next one.
+//
+// A launch takes the longer of one wave's latency and its share of the issue
+// slots.  While the waves of all points fit the chip at once the latency
+// decides, and more lanes per point shorten it: the lane-group kernels with the
+// most lanes (they hold 3 to 4 waves per SIMD, so up to kGroupPts points run
+// at once), then the register kernels with four lanes per point (one wave per
+// SIMD, kFourLanePts points).  Past that the kernel with the fewest
+// instructions per point wins.
+constexpr int64_t kGroupPts = 4096;      // points whose lane-group waves run at once
+constexpr int64_t kFourLanePts = 16384;  // points whose four-lane waves (16 points each) do, one per SIMD
+constexpr int64_t kManyPts = 65536;      // several waves of any register kernel per SIMD
+
+// Lane-group kernels over C: two lanes per work item (half the components
+// each).  32 items per point at n >= 13, where the long ranges have the cuts
+// for them, 16 below (n = 12, d = 6, 3 10^4 points: 281 against 371); d = 7, 8
+// with four lanes per item and 16 items up to n = 13 (n = 12: 393 against 450),
+// at n = 14 two lanes with padded rows (687 against 836 unpadded, whose rows
+// share banks), as at n = 13, d = 9, 10 (729 against 788).  For few points 64 lanes per point (n = 10, d = 4, 1000
+// points: 17 against 20 with 32).
+static const Variant* lane_group_c128(int n, int d, int64_t npts) {
+  const bool few = npts <= kGroupPts / 2;
+  if (d <= 4) {
+    if (few) return n <= 11 ? lane_group_variant(FIELD_C128, 4, 16, 4, true) : lane_group_variant(FIELD_C128, 4, 32, 2, false);
+    return lane_group_variant(FIELD_C128, 4, n >= 13 ? 32 : 16, 2, n < 13);
+  }
+  if (d <= 6) {
+    if (few && n <= 11) return lane_group_variant(FIELD_C128, 8, 16, 4, true);
+    return lane_group_variant(FIELD_C128, 6, few || n >= 13 ? 32 : 16, 2, false);
+  }
+  if (d <= 8) {
+    if (n >= 14 || (n == 13 && npts <= kFourLanePts)) return lane_group_variant(FIELD_C128, 8, 32, 2, true);
+    return lane_group_variant(FIELD_C128, 8, 16, 4, few);
+  }
+  const bool items32 = n >= 13 || (n == 12 && npts <= kGroupPts) || (n == 11 && few);
+  return lane_group_variant(FIELD_C128, 10, items32 ? 32 : 16, 2, n == 13);
+}
+
+// Lane-group kernels over Z_p: one lane per item and 16 items per point for
+// many points (n = 12, d = 8, 10^5 points, unpadded rows: 461 against 534
+// padded), 32 at n = 14 (d = 6: 778 against 827); two lanes per item for few
+// points (n = 11, d = 8, 1000 points: 25 against 46 with 16 lanes per point)
+// and for d = 9, 10 at n = 12, 13 (222 against 231 at 3 10^4 points).
+static const Variant* lane_group_fp(int n, int d, int64_t npts) {
+  if (npts <= kGroupPts / 2) {
+    if (d <= 4) return lane_group_variant(FIELD_FP, 4, 32, 1, false);
+    return lane_group_variant(FIELD_FP, d <= 8 ? 8 : 10, 32, 2, false);
+  }
+  if (npts <= kGroupPts) {
+    if (d <= 4) return lane_group_variant(FIELD_FP, 4, n >= 12 ? 32 : 16, 1, false);
+    if (d > 8) return lane_group_variant(FIELD_FP, 10, n >= 13 ? 32 : 16, 2, false);
+    if (d <= 6 && n >= 13) return lane_group_variant(FIELD_FP, 6, 32, 1, false);
+    return lane_group_variant(FIELD_FP, 8, d > 6 && n >= 13 ? 32 : 16, 2, false);
+  }
+  if (d > 8)
+    return n >= 14 ? lane_group_variant(FIELD_FP, 10, 32, 1, false)
+                   : lane_group_variant(FIELD_FP, 10, 16, n >= 12 ? 2 : 1, false);
+  const int dmax = d <= 4 ? 4 : d <= 6 ? 6 : 8;
+  const bool items32 = n >= 14 && (dmax > 4 || npts <= kManyPts / 2);
+  return lane_group_variant(FIELD_FP, dmax, items32 ? 32 : 16, 1, false);
+}
+
+// Register kernels over C.  Four lanes per point for d = 7, 8 (two components
+// a lane; n = 8, 10^5 points: 158 against 265 with two lanes, whose currents
+// spill), for d = 9, 10 except n = 4 and 6 (n = 7: 141 against 225) and from
+// n = 9 on for d > 4 (n = 9, d = 6: 242 against 266); else two (n = 8, d = 4,
+// 5 10^5 points: 329 against 366).
+static const Variant* register_c128(int n, int d, int64_t npts) {
+  const Variant* four = register_variant(FIELD_C128, n, d, 4);
+  const Variant* two = register_variant(FIELD_C128, n, d, 2);
+  if (!four || !two) return four ? four : two;
+  if (npts <= kFourLanePts || n >= 11) return four;
+  if (d >= 9) return (n == 5 && npts >= kManyPts) || n >= 7 ? four : two;
+  if (d >= 7) return n >= 7 || npts >= kManyPts ? four : two;
+  return d > 4 && n >= 9 ? four : two;
+}
+
+// Register kernels over Z_p.  One lane per point (no sums over lanes, 30 %
+// fewer instructions) for many points of d <= 6 (n = 6, d = 6, 5 10^5 points:
+// 76 against 93), at n = 7, 8 with d = 5, 6 only up to two waves per SIMD
+// (n = 8, d = 6, 10^5 points: 50 against 52; 2 10^5: 98 against 87).  Four for
+// few points, for d = 7, 8 at n <= 5 up to twice as many (3 10^4 points: 7.0
+// against 8.1) and for d = 9, 10 at n = 5, 6 (10^5 points: 33 against 42, 49
+// against 60).  Else two, at n = 7, d = 7, 8 with five components a lane (10^5
+// points: 56 against 67 with four).
+static const Variant* register_fp(int n, int d, int64_t npts) {
+  const Variant* four = register_variant(FIELD_FP, n, d, 4);
+  const Variant* one = register_variant(FIELD_FP, n, d, 1);
+  const Variant* two = register_variant(FIELD_FP, n, d, 2);
+  if (four && npts <= kFourLanePts && (d >= 7 || (d >= 5 && n <= 6))) return four;
+  if (four && (d >= 9 ? n == 5 || n == 6 : d >= 7 && n <= 5 && npts <= 2 * kFourLanePts)) return four;
+  if (one && npts >= kManyPts && (n <= 6 || d <= 4 || npts <= 2 * kManyPts)) return one;
+  if (two && n == 7 && (d == 7 || d == 8) && npts > kFourLanePts) {
+    const Variant* five = register_variant(FIELD_FP, n, 10, 2);
+    if (five) return five;
+  }
+  return two ? two : (one ? one : four);
+}
+
+const Variant* default_variant(int field, int n, int d, int64_t npts) {
+  const Variant* v = nullptr;
+  if (field == FIELD_C128) {
+    // lane-group for few points from n = 7 (d > 4; n = 8, d = 8, 1000 points:
+    // 14 against 49 on two lanes) and where no register kernel is compiled
+    // (n >= 13; n = 12, d > 4; n >= 9, d > 8); at n = 11, d = 8, 10^5 points
+    // the register kernel takes 682, the best lane-group one 840
+    const int64_t few = n >= 9            ? kGroupPts
+                        : n == 8          ? (d > 8 ? kGroupPts : d > 4 ? kGroupPts / 2 : kGroupPts / 4)
+                        : n == 7 && d > 4 ? kGroupPts / 4
+                                          : 0;
+    v = register_c128(n, d, npts);
+    if (!v || npts <= few) v = lane_group_c128(n, d, npts);
+  } else {
+    // lane-group from n = 8 (d > 4) for few points, at n = 11 up to
+    // kFourLanePts (d = 6, 10^4 points: 53 against 74), and there for d > 6 at
+    // any size (d = 8, 10^5 points: 388 against 620: the register kernel
+    // spills) and for d <= 4 from kManyPts on (10^5 points: 249 against 298)
+    const int64_t few = n == 11           ? (d > 6 ? INT64_MAX : kFourLanePts)
+                        : n == 10         ? (d > 6 ? 2 * kGroupPts : kGroupPts)
+                        : n == 9          ? kGroupPts
+                        : n == 8 && d > 4 ? kGroupPts / 4
+                                          : 0;
+    v = register_fp(n, d, npts);
+    if (!v || npts <= few || (n == 11 && d <= 4 && npts >= kManyPts)) v = lane_group_fp(n, d, npts);
+  }
+  if (v) return v;
+  for (const Variant& w : registry())  // whatever covers (field, n, d)
+    if (fits(w, field, n, d)) return &w;
+  return nullptr;
+}
+
+const Variant* choose_variant(int field, int n, int d, int64_t npts) {
   const int idx = pinned(field, n, d, BG_METRIC_MOSTLY_MINUS);
   if (idx >= 0 && idx < (int)registry().size() && fits(registry()[idx], field, n, d))
     return &registry()[idx];
-  return default_variant(field, n, d);
+  return default_variant(field, n, d, npts);
 }
 
-const Variant* default_variant(int field, int n, int d) {
-  const int N = n - 1;
-  const int L = preferred_lanes(field, N, d);
-  const int need = (d + L - 1) / L;
-  const Variant* best = nullptr;
-  for (const Variant& v : registry()) {
-    if (v.generic || v.field != field || v.N != N || v.L != L || v.DL < need) continue;
-    if (best && best->DL == v.DL && !v.lds_tables) continue;  // prefer the LDS-table form on ties
-    if (!best || v.DL < best->DL) best = &v;
-  }
-  if (best) return best;
-  for (const Variant& v : registry()) {  // any register kernel that fits, fewest padded slots
-    if (v.generic || !fits(v, field, n, d)) continue;
-    if (!best || v.DL * v.L < best->DL * best->L || (v.DL * v.L == best->DL * best->L && v.L < best->L))
-      best = &v;
-  }
-  if (best) return best;
-  // runtime-n kernels: the smallest DMAX that covers d; among those the
-  // lane-sharing (wide) form whose resident points fill a CU with the fewest
-  // lanes per point, else the one-point-per-lane form
-  int dmax = 0;
+bool only_lane_groups(int field, int n, int d) {
+  if (pinned(field, n, d, BG_METRIC_MOSTLY_MINUS) >= 0) return true;
   for (const Variant& v : registry())
-    if (v.generic && v.field == field && v.DL >= d && (!dmax || v.DL < dmax)) dmax = v.DL;
-  for (const Variant& v : registry()) {
-    if (!v.generic || v.field != field || v.DL != dmax || v.L == 1) continue;
-    const unsigned per = v.lds_per_point ? v.lds_per_point(N) : 0;
-    const long resident = per ? (long)(max_lds_per_block() / per) * v.L : 0;
-    const bool fills = resident >= 512;
-    if (!best || (fills && (best->L > v.L || !best_fills(best, N))) || (!fills && !best_fills(best, N) && v.L > best->L))
-      best = &v;
-    else if (v.L == best->L && v.padded && !best->padded)
-      best = &v;  // padded rows are compiled only where they avoid bank conflicts
-  }
-  if (best) return best;
-  for (const Variant& v : registry())
-    if (v.generic && v.field == field && v.DL == dmax) return &v;
-  return nullptr;
+    if (!v.generic && fits(v, field, n, d)) return false;
+  return true;
 }
 
 int max_lds_per_block() {
@@ -216,9 +318,21 @@ int max_lds_per_block() {
   return v;
 }
 
+static int cu_count() {
+  static std::once_flag once;
+  static int v = 256;
+  std::call_once(once, [] {
+    int dev = 0, val = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&val, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && val > 0)
+      v = val;
+  });
+  return v;
+}
+
 int prepare(int field, int n, int d, int64_t npts, int64_t ld, const void* momenta, const void* pols,
             void* out, uint8_t* status, const FpConst& fp, LaunchSpec& spec, const Variant* force) {
-  const Variant* v = force ? force : choose_variant(field, n, d);
+  const Variant* v = force ? force : choose_variant(field, n, d, npts);
   if (!v) return BG_ENOTIMPL;
   LaunchArgs& a = spec.args;
   a.momenta = momenta;
@@ -255,6 +369,12 @@ int prepare(int field, int n, int d, int64_t npts, int64_t ld, const void* momen
     if (P >= 64) P = P / 64 * 64;
   } else {
     P = wide_points_per_block(*v, per);
+    // up to one wave per SIMD: the smallest blocks of whole wavefronts, so that
+    // the points spread evenly over the CUs (n = 13, d = 6, 1000 points: 40 us
+    // in blocks of 4 points, 30 us in blocks of one; at 3000 points larger
+    // blocks are faster again, n = 14, d = 6: 59 against 80 us)
+    const int step = v->L < 64 ? 64 / v->L : 1;
+    if (P > step && npts <= (int64_t)4 * cu_count() * step) P = step;
   }
   if (P < 1) return BG_ENOTIMPL;
   const size_t shmem = per * P;
@@ -324,7 +444,7 @@ int launch(int field, int n, int d, int64_t npts, int64_t ld, const void* moment
   const Variant* force = nullptr;
   if (metric == BG_METRIC_ALTERNATING) {
     const int idx = pinned(field, n, d, BG_METRIC_ALTERNATING);
-    force = idx >= 0 ? &registry()[idx] : alternating_variant(choose_variant(field, n, d), field, n, d);
+    force = idx >= 0 ? &registry()[idx] : alternating_variant(choose_variant(field, n, d, npts), field, n, d);
   }
   const int rc = prepare(field, n, d, npts, ld, momenta, pols, out, status, fp, spec, force);
   if (rc != BG_OK) return rc;
@@ -431,7 +551,7 @@ int bg_currents_fp(int n, int d, int64_t npts, int64_t ld, uint32_t p, const uin
 int bg_variants(int field, int n, int d, bg_variant_info* out, int cap) {
   if (field != BG_FIELD_C128 && field != BG_FIELD_FP) return BG_EINVAL;
   if (n < 3 || n > BG_MAX_N || d < 1 || d > BG_MAX_D) return BG_EDOMAIN;
-  const bg::Variant* cur = bg::choose_variant(field, n, d);
+  const bg::Variant* cur = bg::choose_variant(field, n, d, INT64_MAX);
   int count = 0;
   const auto& reg = bg::registry();
   for (int i = 0; i < (int)reg.size(); ++i) {

@@ -1,9 +1,10 @@
 // Batched launches over mixed (field, n, d) groups: bg_batch_run and the
 // hipGraph plans bg_batch_plan_*.
 //
-// Queue form (BG_BATCH_QUEUE).  The groups whose selected kernel is a
-// lane-group (runtime-n) kernel are served by one persistent launch per such
-// kernel variant instead of one launch per group: the variant's blocks stay
+// Queue form (BG_BATCH_QUEUE).  The groups whose (field, n, d) no register
+// kernel serves, or that are pinned to a lane-group (runtime-n) kernel, are
+// served by one persistent launch per such kernel variant instead of one launch
+// per group: the variant's blocks stay
 // resident and take (group, point range) tiles from a device work queue, one
 // atomic increment per tile, with the groups ordered by cost per point so the
 // longest tiles go first.  Register-kernel groups launch as before.  The
@@ -12,7 +13,7 @@
 // it stream-ordered for the call, a plan at creation, and
 // bg_batch_run_noalloc uses a fixed device array of the library instead.
 //
-// Every group runs the kernel variant selected for its (field, n, d) (the
+// Every group runs the kernel that a single call of its size runs (the
 // autotuner's pin, else the default).  Groups are ordered longest first by
 // estimated work and spread over a few internal streams (greedy, least loaded
 // first), forked from and joined back to the caller's stream, so small groups
@@ -144,7 +145,9 @@ int plan_queue(const bg_group* groups, int ngroups, QueuePlan& qp) {
   std::vector<std::vector<const Prepared*>> members;
   for (const Prepared& w : work) {
     const Variant* v = w.spec.variant;
-    if (!(w.spec.generic && v && v->fn_queue && v->lds_per_point)) {
+    // a group that takes a lane-group kernel instead of a register kernel of
+    // its (field, n, d) launches by itself, as that register kernel would
+    if (!(w.spec.generic && v && v->fn_queue && v->lds_per_point && only_lane_groups(w.field, w.n, w.d))) {
       qp.direct.push_back(w);
       continue;
     }
@@ -307,7 +310,7 @@ int run_units(std::vector<Unit>& units, QueuePlan& qp, unsigned char* buf, hipSt
 // its own copy until the process ends.  Host code must not use the array's
 // name as an address: its device address comes from hipGetSymbolAddress,
 // once per device.
-constexpr size_t kQueueScratchBytes = 256 * 1024;
+constexpr size_t kQueueScratchBytes = 264 * 1024;
 __device__ __align__(256) unsigned char scratch[kQueueScratchBytes];
 
 std::mutex g_scratch_mu;

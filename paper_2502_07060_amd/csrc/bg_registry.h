@@ -60,7 +60,13 @@ FpConst make_fp_const(uint32_t p);
 // a square root of -1 mod p (p = 1 mod 4) times R = 2^64, balanced
 int32_t fp_sqrt_minus_one_mont(uint32_t p);
 bool is_prime_u32(uint32_t n);
-// force: the variant to launch instead of the one selected for (field, n, d)
+// the variant a call of npts points runs: the pin of (field, n, d), else the
+// default for that size
+const Variant* choose_variant(int field, int n, int d, int64_t npts);
+// whether no register kernel serves (field, n, d), or a pin decides: only the
+// groups of such (field, n, d) are queue candidates
+bool only_lane_groups(int field, int n, int d);
+// force: the variant to launch instead of the one chosen for (field, n, d, npts)
 int prepare(int field, int n, int d, int64_t npts, int64_t ld, const void* momenta, const void* pols,
             void* out, uint8_t* status, const FpConst& fp, LaunchSpec& spec, const Variant* force = nullptr);
 int enqueue(LaunchSpec& spec, hipStream_t stream);
