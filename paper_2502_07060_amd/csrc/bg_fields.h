@@ -71,13 +71,6 @@ struct FpField {
     else return time_lane ? -x : x;
   }
   __device__ __forceinline__ E esub(E a, E b) const { return fp_sub(a, b, k); }
-  // small fold constant only: |x| <= 2h (an int32 difference of balanced
-  // values) -> the same residue with |result| <= h + 2^23, by one product with
-  // 2^32 mod p (below 2^53) and one 32-bit REDC step (x c32 2^-32 = x mod p)
-  __device__ __forceinline__ E lazy_norm(int32_t x) const {
-    static_assert(SC, "needs |2^32 mod p| <= 2^22");
-    return fp_redc1(mul64(x, k.c32), k);
-  }
   __device__ __forceinline__ E eadd(E a, E b) const { return fp_add(a, b, k); }
   __device__ __forceinline__ S sneg(S a) const { return -a; }
   __device__ __forceinline__ S szero() const { return 0; }
@@ -101,8 +94,9 @@ struct FpField {
   // (|J| <= h + 2^23, from two 32-bit REDC steps, see finish_mul32), so
   // UX = 2 counts a product of two such values, (h + 2^23)^2 < 2^60 + 2^55
   // (66 units), and UX = 4 an unreduced difference times one, 2h (h + 2^23)
-  // < 2^61 + 2^54 (129); UX = 5 (both operands lazily normalised) is 66 too.
-  static constexpr int ux_units(int UX) { return SC ? (UX == 4 ? 129 : 66) : UX; }
+  // < 2^61 + 2^54 (129); UX = 6: both operands unreduced differences, (2h)^2 <
+  // 2^62 (256).
+  static constexpr int ux_units(int UX) { return SC ? (UX == 6 ? 256 : UX == 4 ? 129 : 66) : UX; }
   static constexpr int uz_units(int UZ) { return SC ? (UZ == 3 ? 1 : 64) : UZ; }
   // products that enter a current's accumulator (SC schedule only; vectors
   // are currents (|.| <= h + 2^23) or balanced prefix sums)
@@ -255,19 +249,14 @@ struct FpField {
   }
 
   __device__ __forceinline__ E finish(A K) const { return fp_redc2(fp_fold(K, k), k); }
-  // finish(K) * c for a c carrying an extra factor 2^-32 (one 32-bit REDC step
-  // instead of a full one before the product).  Small fold constant: the
+  // finish(K) * c for a c in (-p, p) carrying an extra factor 2^-32 (one 32-bit
+  // REDC step instead of a full one before the product: below 1.5 2^30, so the
+  // product stays below 1.5 2^61).  Small fold constant: the
   // product is finished with one more fold and 32-bit REDC step instead of
   // REDC2 (c then carries 2^-64, see Inverses), leaving |J| <= h + 2^22.
   __device__ __forceinline__ E finish_mul32(A K, S c) const {
     if constexpr (SC) return fp_redc1(fp_fold(mul64(fp_redc1(fp_fold(K, k), k), c), k), k);
     else return fp_redc2(mul64(fp_redc1(fp_fold(K, k), k), c), k);
-  }
-  // small fold constant: a b 2^-32 mod p for |a|, |b| <= h + 2^23 (a product
-  // in the Montgomery domain of 2^32), result |.| <= h + 2^22
-  __device__ __forceinline__ S mulp(S a, S b) const {
-    static_assert(SC, "needs |2^32 mod p| <= 2^22");
-    return fp_redc1(fp_fold(mul64(a, b), k), k);
   }
   __device__ __forceinline__ E mul(E x, S c) const { return fp_mul(x, c, k); }
   __device__ __forceinline__ S smul(S a, S b) const { return fp_mul(a, b, k); }

@@ -118,17 +118,18 @@ struct Loader<FpField<DL, L, SC>> {
     const uint32_t x =
         static_cast<const uint32_t*>(base)[((int64_t)l * a.d + (in ? mu : 0)) * a.ld + q];
     const uint32_t xi = in ? x : 0u;
+    // a residue >= p goes on as it is: its point's result is replaced by the
+    // sentinel, whatever the arithmetic makes of it
     maxraw = maxraw > xi ? maxraw : xi;
-    const uint32_t xc = xi < (uint32_t)a.fp.p ? xi : 0u;
     const bool rot = mu >= 2 && (mu & 1) == 0;
     if constexpr (M == MetricRT) {
       // one product for every component, with R (the conversion, bit for bit:
       // both results are balanced) or with a.ialt: a select between a product
       // and the conversion became a branch around each load, which then
       // waited for every load before issuing the next
-      return fp_mul((int32_t)xc, rot ? a.ialt : a.fp.one, a.fp);
+      return fp_mul((int32_t)xi, rot ? a.ialt : a.fp.one, a.fp);
     } else {
-      int32_t v = fp_from_canonical(xc, a.fp);
+      int32_t v = fp_from_canonical(xi, a.fp);
       if constexpr (M == MetricAlt) {  // a select, so that the loads stay in one block
         const int32_t w = fp_mul(v, a.ialt, a.fp);
         v = rot ? w : v;
@@ -159,7 +160,7 @@ struct Loader<C128Field<DL, L>> {
 };
 
 // ---------------------------------------------------------------------------
-// propagator inverses: inv'(S) = 2 / P_S^2, given y(S) = -P_S^2
+// propagator inverses: inv'(S) = -2 / P_S^2, given y(S) = -P_S^2
 // ---------------------------------------------------------------------------
 template <class Fld, int NP>
 struct Inverses {};
@@ -168,23 +169,23 @@ template <int DL, int L, bool SC, int NP>
 struct Inverses<FpField<DL, L, SC>, NP> {
   // Montgomery batch inversion (Montgomery 1987): one Fermat power for all NP
   // values; a zero anywhere makes the point singular.  inv(s) receives
-  // 2/P_S^2 for y(s) = -P_S^2, as the finish of each current expects it.
+  // -2/P_S^2 for y(s) = -P_S^2, as the finish of each current (of -K')
+  // expects it.
   //
-  // General schedule: products are Montgomery products with R = 2^64 (fp_mul).
-  // Small fold constant: products are taken in the Montgomery domain of 2^32
-  // (mulp: a b 2^-32, one fold and one 32-bit REDC step), with 1 = 2^32 mod
-  // p.  There y(s) = -P^2 R stands for -P^2 2^32, so its inverse comes out as
-  // the plain residue -1/P^2, and the final product with the plain residue -2
-  // gives 2/P^2 2^-32, the extra 2^-32 that the small-fold finish needs.
+  // Products are taken in the Montgomery domain of 2^32 (fp_mul32, three
+  // instructions; the 3 NP + 60 of them took five each with REDC2 or a fold).
+  // There 1 = 2^32 mod p, and y's inverse comes out as R/y (R = 2^64); y
+  // itself stands for -P^2 R, so that is the plain residue of -1/P^2.  General
+  // schedule: the factor 2 in Montgomery form (2^33) gives -2/P^2.  Small fold
+  // constant: the plain factor 2 gives -2/P^2 2^-32, the extra 2^-32 that the
+  // small-fold finish needs.  The results lie in (-p, p), which both finishes
+  // take.
   template <class Tab>
   __device__ static bool compute(const FpField<DL, L, SC>& F, int32_t (&y)[NP > 0 ? NP : 1], Tab& inv) {
     if constexpr (NP == 0) {
       return false;
     } else {
-      auto mul = [&](int32_t a, int32_t b) {
-        if constexpr (SC) return F.mulp(a, b);
-        else return fp_mul(a, b, F.k);
-      };
+      auto mul = [&](int32_t a, int32_t b) { return fp_mul32(a, b, F.k); };
       bool zero = false;
       int32_t pre[NP];
 #pragma unroll
@@ -199,19 +200,18 @@ struct Inverses<FpField<DL, L, SC>, NP> {
       // carried across a loop were multiplied with the generic 64-bit sequence
       // instead of one v_mad_i64_i32).
       const uint32_t e = (uint32_t)(F.k.p - 2);
-      int32_t t = SC ? F.k.c32 : F.k.one;
+      int32_t t = F.k.c32;
 #pragma unroll
       for (int b = 30; b >= 0; --b) {
         t = mul(t, t);
         const int32_t m = mul(t, pre[NP - 1]);
         t = ((e >> b) & 1u) ? m : t;
       }
-      // the factor -2 turns 1/y = -1/P^2 into 2/P^2 for every element.  It
-      // is applied as the plain residue 2 (the constant 2 times R^-1), which
-      // removes both the 2^32 that lazily reduced scalars leave in the current
+      // the factor 2 for every element.  As the plain residue it also removes
+      // both the 2^32 that lazily reduced scalars leave in the current
       // accumulators and the 2^-32 of the single 32-bit REDC step that
       // finishes each current (FpField::finish_mul32)
-      t = mul(t, -2);
+      t = mul(t, SC ? 2 : F.k.two32);
 #pragma unroll
       for (int s = NP - 1; s >= 0; --s) {
         inv.set(s, s == 0 ? t : mul(t, pre[s - 1]));
@@ -342,11 +342,13 @@ struct Recursion {
           constexpr int j = i + m - 1;
           E Pp[DL], P[DL];
           if constexpr (Fld::kSC) {
-            // P_S lazily normalised (|slot| <= h + 2^23): 66 units a product
+            // P_S as unreduced differences: 256 units a product, so a fold
+            // (two instructions) after each instead of normalising each
+            // component (three)
 #pragma unroll
-            for (int c = 0; c < DL; ++c) P[c] = F.lazy_norm(Qg(j + 1, c) - Qg(i, c));
+            for (int c = 0; c < DL; ++c) P[c] = Qg(j + 1, c) - Qg(i, c);
             unprime(F, P, Pp);
-            y[R::pidx(i, j)] = F.template ndot<5>(Pp, P);
+            y[R::pidx(i, j)] = F.template ndot<6>(Pp, P);
           } else {
             primedP<i, j>(F, mom, Pp);
             unprime(F, Pp, P);
@@ -387,6 +389,10 @@ struct Recursion {
 #pragma unroll
           for (int c = 0; c < DL; ++c) Pp[c] = col[i][c];
         }
+        // F_p: K accumulates -K', whose terms take the negated dot products as
+        // they come (only one of a three-gluon split's three axpys, and no
+        // four-gluon one, needs a negated scalar); the propagator inverse
+        // carries the sign back
         A K[DL];
 #pragma unroll
         for (int c = 0; c < DL; ++c) K[c] = F.azero();
@@ -448,9 +454,9 @@ struct Recursion {
             if constexpr (kMergeDh && t + 1 < j)
               nc3 = F.template ndot_sub2<4, 3, true>(Pp, J[ib], cur.cb, F.sneg(cur.db));
             else nc3 = F.template ndot_sub<4, 3, true>(Pp, J[ib], cur.cb);
-            F.template kaxpy<Fld::kPLazy>(K, uK, F.sneg(nDm), cur.v);          // times Q_{t+1}
-            F.template kaxpy<Fld::kPLazy>(K, uK, F.sneg(nc2), J[ib]);
-            F.template kaxpy<Fld::kPLazy>(K, uK, nc3, J[ia]);
+            F.template kaxpy<Fld::kPLazy>(K, uK, nDm, cur.v);          // times Q_{t+1}
+            F.template kaxpy<Fld::kPLazy>(K, uK, nc2, J[ib]);
+            F.template kaxpy<Fld::kPLazy>(K, uK, F.sneg(nc3), J[ia]);
             F.fixed_fold(K);
           } else {
 #pragma unroll
@@ -488,7 +494,7 @@ struct Recursion {
           E QQ[DL];
 #pragma unroll
           for (int c = 0; c < DL; ++c) QQ[c] = Qg(i, c) + Qg(j + 1, c);
-          F.template kaxpy<Fld::kPBalDiff>(K, uK, nDhS, QQ);
+          F.template kaxpy<Fld::kPBalDiff>(K, uK, F.sneg(nDhS), QQ);
           F.fixed_fold(K);
         } else {
           // stored as its L-th part (the splits that read it start their
@@ -504,7 +510,7 @@ struct Recursion {
           static_for<s1 + 1, j>([&](auto tc) {
             constexpr int t = decltype(tc)::value;
             const S ne = F.template ndot_u<kFp>(J[R::idx(i, s1)], J[R::idx(t + 1, j)]);  // F_p: lazy
-            F.template kaxpy<Fld::kPLazy>(K, uK, F.sneg(ne), J[R::idx(s1 + 1, t)]);
+            F.template kaxpy<Fld::kPLazy>(K, uK, kFp ? ne : F.sneg(ne), J[R::idx(s1 + 1, t)]);
             constexpr int qn = v4_index<i, j>(s1, t);
             // F_p, general schedule: lazy scalars give products below 3
             // half-units: fold every third
@@ -516,13 +522,13 @@ struct Recursion {
         if constexpr (!kMergeDh) {
           static_for<i + 1, j>([&](auto tc) {
             constexpr int t = decltype(tc)::value;
-            F.template kaxpy<Fld::kPBal>(K, uK, nDh.get(R::pidx(i, t)), J[R::idx(t + 1, j)]);
+            F.template kaxpy<Fld::kPBal>(K, uK, F.sneg(nDh.get(R::pidx(i, t))), J[R::idx(t + 1, j)]);
             if constexpr ((t - i) % 5 == 4) F.fixed_fold(K);
           });
           F.fixed_fold(K);
           static_for<i, j - 1>([&](auto sc) {
             constexpr int s1 = decltype(sc)::value;
-            F.template kaxpy<Fld::kPBal>(K, uK, nDh.get(R::pidx(s1 + 1, j)), J[R::idx(i, s1)]);
+            F.template kaxpy<Fld::kPBal>(K, uK, F.sneg(nDh.get(R::pidx(s1 + 1, j))), J[R::idx(i, s1)]);
             if constexpr ((s1 - i) % 5 == 4) F.fixed_fold(K);
           });
         }
@@ -548,7 +554,8 @@ struct Recursion {
             for (int c = 0; c < DL; ++c) J[id][c] = F.mul(F.finish(K[c]), inv2);
           }
         } else {
-          // a6: returns -(eps_n . K'); the amplitude is M = 2 eps_n . K'
+          // a6: returns -(eps_n . K') (F_p: eps_n . K', and -K' as the root
+          // current); the amplitude is M = 2 eps_n . K'
           E Kf[DL];
 #pragma unroll
           for (int c = 0; c < DL; ++c) Kf[c] = F.finish(K[c]);
@@ -656,8 +663,8 @@ void bg_recursion_kernel(LaunchArgs a) {
     bad = bad >= (uint32_t)a.fp.p ? 1u : 0u;
     const uint8_t st = bad ? PT_BADRESIDUE : (singular ? PT_SINGULAR : PT_OK);
     if (a.cur) {
-      // root current K = 2 K'; kroot carries R^-3 (degree n - 1 in eps, 4 - n
-      // in k) and the accumulator's 2^32: one product with R^3 2^-32 restores it
+      // root current K = 2 K' = -2 kroot; kroot carries R^-3 (degree n - 1 in eps,
+      // 4 - n in k) and the accumulator's 2^32: one product with R^3 2^-32 restores it
       if (valid) {
 #pragma unroll
         for (int c = 0; c < DL; ++c) {
@@ -666,7 +673,7 @@ void bg_recursion_kernel(LaunchArgs a) {
             uint32_t v = 0xFFFFFFFFu;
             if (st == PT_OK) {
               const int32_t m = fp_mul(kroot[c], a.fp.r3s, a.fp);
-              v = fp_to_canonical(fp_add(m, m, a.fp), a.fp);
+              v = fp_to_canonical(fp_sub(0, fp_add(m, m, a.fp), a.fp), a.fp);
             }
             static_cast<uint32_t*>(a.cur)[(int64_t)mu * a.ld + q] = v;
           }
@@ -676,11 +683,11 @@ void bg_recursion_kernel(LaunchArgs a) {
     } else if (valid && s == 0) {
       uint32_t outv = 0xFFFFFFFFu;
       if (st == PT_OK) {
-        // res = -(eps_n . K') in Montgomery form of a value scaled by R^-4,
-        // times the 2^32 that the root accumulator carries; M = 2 eps_n . K'
-        // = res * (-2), times R^4 2^-32 to undo both scalings.
+        // res = eps_n . K' in Montgomery form of a value scaled by R^-4, times
+        // the 2^32 that the root accumulator carries; M = 2 eps_n . K' = 2 res,
+        // times R^4 2^-32 to undo both scalings.
         int32_t m = fp_mul(res, a.fp.r4s, a.fp);
-        m = fp_sub(0, fp_add(m, m, a.fp), a.fp);     // * (-2)
+        m = fp_add(m, m, a.fp);
         outv = fp_to_canonical(m, a.fp);
       }
       static_cast<uint32_t*>(a.out)[q] = outv;

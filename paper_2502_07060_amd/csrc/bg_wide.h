@@ -339,22 +339,24 @@ struct WideRecursion {
         Pu[0] = F.prime0(Pp[0]);
         int32_t y = F.ndot(Pp, Pu);
         if (y == 0) { singular = true; y = F.k.one; }
-        acc = any ? fp_mul(acc, y, F.k) : y;
+        acc = any ? fp_mul32(acc, y, F.k) : y;
         any = true;
         invt[id] = y;
         nDht[id] = acc;
       }
       if (any) {
-        int32_t t = fp_pow(acc, (uint32_t)(F.k.p - 2), F.k);
-        // 1/y = -1/P^2 -> 2/P^2, with the extra 2^-32 that finish_mul32 expects
-        t = fp_mul(t, -F.k.two32, F.k);
+        // products of three instructions in the Montgomery domain of 2^32: y's
+        // inverse there is R/y, and the factor -2 R 2^-32 turns -R/P^2 R^-1 into
+        // 2/P^2 with the extra 2^-32 that finish_mul32 expects
+        int32_t t = fp_pow32(acc, (uint32_t)(F.k.p - 2), F.k);
+        t = fp_mul32(t, -F.k.two, F.k);
         int last = g;
         while (last + G < np) last += G;
         for (int r = last; r >= g; r -= G) {
           const int id = N + r;
           const int32_t y = invt[id];
-          invt[id] = r > g ? fp_mul(t, nDht[id - G], F.k) : t;
-          t = fp_mul(t, y, F.k);
+          invt[id] = r > g ? fp_mul32(t, nDht[id - G], F.k) : t;
+          t = fp_mul32(t, y, F.k);
         }
       }
     }
