@@ -275,11 +275,11 @@ struct WideRecursion {
     if (ln == 0) *flags = 0u;
     if (ln < N) nDht[rid(ln, ln)] = S{};  // a single leg has no two-way split
     group_sync();
-    if (ln < DMAX) {  // prefix sums, one component per lane: all legs read first
-      E k[kLegs];
+    if constexpr (kFp) {
+      if (ln < DMAX) {  // prefix sums, one component per lane: all legs read first
+        E k[kLegs];
 #pragma unroll
-      for (int l = 0; l < kLegs; ++l) k[l] = l < N ? Mat(l + 1, ln) : E{};
-      if constexpr (kFp) {
+        for (int l = 0; l < kLegs; ++l) k[l] = l < N ? Mat(l + 1, ln) : E{};
         E acc{};
         Mat(0, ln) = acc;
 #pragma unroll
@@ -289,23 +289,32 @@ struct WideRecursion {
             Mat(l + 1, ln) = acc;
           }
         }
-      } else {
-        // hi + lo = Q_l exactly up to the rounding of lo: hi takes the
-        // two-sum with each leg, lo collects the rounding errors
-        double hr = 0.0, hm = 0.0, lr = 0.0, lm = 0.0;
-        Mat(0, ln) = cplx{0.0, 0.0};
-        Mlo(0, ln) = cplx{0.0, 0.0};
+      }
+    } else {
+      // prefix sums, a real or imaginary part per lane (16 lanes and d = 10: two
+      // parts in some of them)
 #pragma unroll
-        for (int l = 0; l < kLegs; ++l) {
-          if (l < N) {
-            const double sr = hr + k[l].re, br = sr - hr;
-            lr += (hr - (sr - br)) + (k[l].re - br);
-            hr = sr;
-            const double sm = hm + k[l].im, bm = sm - hm;
-            lm += (hm - (sm - bm)) + (k[l].im - bm);
-            hm = sm;
-            Mat(l + 1, ln) = cplx{hr, hm};
-            Mlo(l + 1, ln) = cplx{lr, lm};
+      for (int x0 = 0; x0 < 2 * DMAX; x0 += G * LC) {
+        if (x0 + ln < 2 * DMAX) {
+          double* const hi = reinterpret_cast<double*>(Mt) + x0 + ln;
+          double* const lo = reinterpret_cast<double*>(Ml) + x0 + ln;
+          double k[kLegs];
+#pragma unroll
+          for (int l = 0; l < kLegs; ++l) k[l] = l < N ? hi[(l + 1) * 2 * kS] : 0.0;
+          // hi + lo = Q_l exactly up to the rounding of lo: hi takes the two-sum
+          // with each leg, lo collects the rounding errors
+          double h = 0.0, r = 0.0;
+          hi[0] = 0.0;
+          lo[0] = 0.0;
+#pragma unroll
+          for (int l = 0; l < kLegs; ++l) {
+            if (l < N) {
+              const double sum = h + k[l], b = sum - h;
+              r += (h - (sum - b)) + (k[l] - b);
+              h = sum;
+              hi[(l + 1) * 2 * kS] = h;
+              lo[(l + 1) * 2 * kS] = r;
+            }
           }
         }
       }
@@ -318,6 +327,35 @@ struct WideRecursion {
         loadJ(rid(l, l), e);
         nct[rid(l, l)] = F.template ndot<4>(Pp, e);
       }
+    }
+  }
+
+  // ---- complex: 2 / P_S^2 for every 2 <= |S| <= N-1, ahead of the recursion,
+  // into the slot of nDh(S), which S's finish reads before it writes nDh(S).
+  // A length m and the length N + 2 - m have N ranges together, so entry t of
+  // row m - 2 is range t of length m or, past those, of the other length: the
+  // items take N floor(N / 2) entries in turn (N = 13: 78 entries, 3 rounds of
+  // 32 items).  Done in the rounds of the recursion instead, every item of a
+  // round repeats its range's division (11 rounds at N = 13).  With the prefix
+  // sums below in twice the lanes, 163016 points of n = 14, d = 6 take 2410 us
+  // after 2485 us, 63438 of d = 4 719 us after 751 us.
+  __device__ void propagators(const Fld& F, bool& singular) {
+    const int entries = N * (N / 2);
+    const uint32_t rec = 65536u / (uint32_t)N + 1u;  // e / N = e rec >> 16, exact for e N < 65536
+    for (int e = g; e < entries; e += G) {
+      const int row = (int)(((uint32_t)e * rec) >> 16), t = e - row * N;
+      const int n1 = N - 1 - row;  // ranges of length row + 2
+      const int m = t < n1 ? row + 2 : N - row, i = t < n1 ? t : t - n1;
+      // the middle length's row has no second half; the root has no propagator
+      if ((t >= n1 && m <= row + 2) || m >= N) continue;
+      E Qih[DL], Qil[DL], Qjh[DL], Qjl[DL], P[DL], Pu[DL];
+      loadQ(i, Qih, Qil);
+      loadQ(i + m, Qjh, Qjl);
+      dd_diff(Qih, Qil, Qjh, Qjl, P);
+#pragma unroll
+      for (int c = 0; c < DL; ++c) Pu[c] = P[c];
+      Pu[0] = F.prime0(P[0]);
+      nDht[rid(i, i + m - 1)] = Rec::c_inverse_times(F.ndot(P, Pu), -2.0, singular);
     }
   }
 
@@ -416,28 +454,33 @@ struct WideRecursion {
     loadJ(rid(i, c1), JA);
     const int n1 = j - c1 - 1;
     const int nt = n1 + (c2 != c1 ? j - c2 - 1 : 0);
-    int rm = rid(c1 + 1, c1 + 1), lm = 0;
-    int rc = rid(c1 + 2, j), lc = j - c1 - 2;
+    // rows of [c+1..t] and [t+1..j] and what they advance by, in bytes: two
+    // additions per split and row instead of an index, a product and an offset
+    constexpr int kRow = kS * (int)sizeof(E);
+    const char* const base = reinterpret_cast<const char*>(Jt + co);
+    int am = rid(c1 + 1, c1 + 1) * kRow, dm = N * kRow;
+    int ac = rid(c1 + 2, j) * kRow, dc = (j - c1 - 2 - N) * kRow;
     int cnt = 0;
 #pragma unroll 2
     for (int q = 0; q < nt; ++q) {
       if (q == n1) {  // on to cut c2 (only reached when it has splits)
         loadJ(rid(i, c2), JA);
-        rm = rid(c2 + 1, c2 + 1);
-        lm = 0;
-        rc = rid(c2 + 2, j);
-        lc = j - c2 - 2;
+        am = rid(c2 + 1, c2 + 1) * kRow;
+        dm = N * kRow;
+        ac = rid(c2 + 2, j) * kRow;
+        dc = (j - c2 - 2 - N) * kRow;
       }
       E JM[DL], JC[DL];
-      loadJ(rm, JM);
-      loadJ(rc, JC);
+      load_row(reinterpret_cast<const E*>(base + am), JM);
+      load_row(reinterpret_cast<const E*>(base + ac), JC);
       const S ne = F.ndot_u(JA, JC);
       F.axpy(K, F.sneg(ne), JM);
-      if (++cnt == 5) { F.fold(K); cnt = 0; }
-      rm += N - lm;
-      ++lm;
-      rc += lc - N;
-      --lc;
+      if constexpr (kFp)
+        if (++cnt == 5) { F.fold(K); cnt = 0; }
+      am += dm;
+      dm -= kRow;
+      ac += dc;
+      dc -= kRow;
     }
     F.fold(K);
   }
@@ -465,7 +508,8 @@ struct WideRecursion {
     uint32_t bad = 0;
     bool singular = false;
     load(F, a, q, bad);
-    inverses(F, singular);
+    if constexpr (kFp) inverses(F, singular);
+    else propagators(F, singular);
     group_sync();
 
     for (int m = 2; m <= N; ++m) {
@@ -482,9 +526,9 @@ struct WideRecursion {
 #pragma unroll
         for (int c = 0; c < DL; ++c) K[c] = F.azero();
         NDS nDs{};
-        // what the range's finish needs and K does not (P_S, the propagator
-        // inverse, F_p: Q_i + Q_{j+1}): formed before the cuts, so that its
-        // loads and the division overlap their work
+        // F_p: what the range's finish needs and K does not (P_S, the propagator
+        // inverse, Q_i + Q_{j+1}): formed before the cuts, so that its loads
+        // overlap their work
         E Pp[DL], QQ[DL];
         S inv2{};
         if constexpr (kFp) {
@@ -505,14 +549,6 @@ struct WideRecursion {
             E Qih[DL], Qil[DL], Qjh[DL], Qjl[DL], Qch[DL], Qcl[DL], PA[DL], PB[DL];
             loadQ(i, Qih, Qil);
             loadQ(j + 1, Qjh, Qjl);
-            dd_diff(Qih, Qil, Qjh, Qjl, Pp);
-            if (m < N) {  // the root has no propagator
-              E Pu[DL];
-#pragma unroll
-              for (int c = 0; c < DL; ++c) Pu[c] = Pp[c];
-              Pu[0] = F.prime0(Pp[0]);
-              inv2 = Rec::c_inverse_times(F.ndot(Pp, Pu), -2.0, singular);
-            }
             loadQ(c1 + 1, Qch, Qcl);
             dd_diff(Qih, Qil, Qch, Qcl, PA);
             dd_diff(Qch, Qcl, Qjh, Qjl, PB);
@@ -547,6 +583,7 @@ struct WideRecursion {
             nDhS = cplx{kPart * nDs.re, kPart * nDs.im};
           }
           if (m < N) {
+            if constexpr (!kFp) inv2 = nDht[id];
             nDht[id] = nDhS;
             E Jn[DL];
 #pragma unroll
