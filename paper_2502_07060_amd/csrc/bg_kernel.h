@@ -82,7 +82,9 @@ constexpr unsigned kQueueLdsHeader = 16;  // LDS bytes before the points' tables
 // ---------------------------------------------------------------------------
 // Every load is unconditional (a padded component reads row 0 and is zeroed
 // afterwards), so the compiler can issue all of a point's loads back to back
-// and wait once.  On F_p the largest raw residue seen is kept in `maxraw`;
+// and wait once.  Complex: get() is fix() of what was read; a kernel that reads its
+// next point early (Recursion::Raw) keeps the values as they were read and
+// calls fix() when it takes them.  On F_p the largest raw residue seen is kept in `maxraw`;
 // the point has a bad residue iff it ends up >= p.
 //
 // Alternating metric (paper Sec. 3.1, diag(1, -1, 1, -1, ...)).  Multiplying
@@ -144,9 +146,13 @@ struct Loader<C128Field<DL, L>> {
   template <int M>
   __device__ static cplx get(const LaunchArgs& a, const void* base, int l, int mu, int64_t q,
                              uint32_t&) {
+    return fix<M>(a, mu,
+                  static_cast<const double2*>(base)[((int64_t)l * a.d + (mu < a.d ? mu : 0)) * a.ld + q]);
+  }
+  // the component of a value that was read
+  template <int M>
+  __device__ static cplx fix(const LaunchArgs& a, int mu, double2 v) {
     const bool in = mu < a.d;
-    const double2 v =
-        static_cast<const double2*>(base)[((int64_t)l * a.d + (in ? mu : 0)) * a.ld + q];
     // selects, not branches: an early return here lets the compiler sink each
     // load into a block of its own, which serialises the point's loads.
     // Component 0 is multiplied by i (C128Field holds time components that
@@ -276,9 +282,42 @@ struct Recursion {
     }
   }
 
-  template <int BLOCK, int M>
+  // Complex: a point's momenta and polarisations 1 .. N as they were read (eps_n, which
+  // only the root uses, is read by the point itself).  The rows advance by a
+  // stride that every lane shares: row addresses of their own are invariant in
+  // a loop over points, and 2 N DL of them kept in registers spill.
+  struct Raw {
+    double2 k[N][DL], e[N][DL];
+    __device__ __forceinline__ void read(const LaunchArgs& a, int64_t q, int mu0) {
+      const double2* pk[DL];
+      const double2* pe[DL];
+#pragma unroll
+      for (int c = 0; c < DL; ++c) {
+        const int64_t at = (int64_t)(mu0 + c < a.d ? mu0 + c : 0) * a.ld + q;
+        pk[c] = static_cast<const double2*>(a.momenta) + at;
+        pe[c] = static_cast<const double2*>(a.pols) + at;
+      }
+      const int64_t row = (int64_t)a.d * a.ld;
+#pragma unroll
+      for (int l = 0; l < N; ++l) {
+#pragma unroll
+        for (int c = 0; c < DL; ++c) {
+          k[l][c] = *pk[c];
+          e[l][c] = *pe[c];
+          pk[c] += row;
+          pe[c] += row;
+        }
+      }
+    }
+  };
+
+  // raw: the point's inputs, read earlier; once they are taken it is refilled
+  // with the inputs of point qnext, which the loop over points wants next.
+  // Without it (null) the point reads its own.
+  template <int BLOCK, int M, bool STREAM = false>
   __device__ static void run(const Fld& F, const LaunchArgs& a, int64_t q, int s, uint32_t& bad,
-                             bool& singular, S& result, E (&kroot)[DL], Lds<BLOCK>* lds) {
+                             bool& singular, S& result, E (&kroot)[DL], Lds<BLOCK>* lds,
+                             [[maybe_unused]] Raw* raw = nullptr, [[maybe_unused]] int64_t qnext = 0) {
     constexpr bool kFp = Fld::exact;
     E J[NCUR][DL];
     E epsn[DL];
@@ -315,8 +354,13 @@ struct Recursion {
       E k[DL];
 #pragma unroll
       for (int c = 0; c < DL; ++c) {
-        k[c] = Loader<Fld>::template get<M>(a, a.momenta, l, mu0 + c, q, bad);
-        J[R::idx(l, l)][c] = Loader<Fld>::template get<M>(a, a.pols, l, mu0 + c, q, bad);
+        if constexpr (STREAM) {
+          k[c] = Loader<Fld>::template fix<M>(a, mu0 + c, raw->k[l][c]);
+          J[R::idx(l, l)][c] = Loader<Fld>::template fix<M>(a, mu0 + c, raw->e[l][c]);
+        } else {
+          k[c] = Loader<Fld>::template get<M>(a, a.momenta, l, mu0 + c, q, bad);
+          J[R::idx(l, l)][c] = Loader<Fld>::template get<M>(a, a.pols, l, mu0 + c, q, bad);
+        }
       }
       k[0] = F.prime0(k[0]);
       if constexpr (kFp) {
@@ -331,6 +375,11 @@ struct Recursion {
     });
 #pragma unroll
     for (int c = 0; c < DL; ++c) epsn[c] = Loader<Fld>::template get<M>(a, a.pols, N, mu0 + c, q, bad);
+    if constexpr (STREAM) {
+      split_barrier();  // the reads start here, ahead of the recursion
+      raw->read(a, qnext, mu0);
+      split_barrier();
+    }
 
     // ---- a3/a4 (F_p): all propagator denominators, one batched inversion -----
     if constexpr (kFp) {
@@ -637,26 +686,12 @@ struct Recursion {
   }
 };
 
-// W = minimum waves per SIMD the register allocation must allow (1: the whole
-// register file for one wave; 2: at most 256 registers per lane).
-template <class Fld, int N, int DL, int L, int BLOCK, bool LT, int W>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W)))
-void bg_recursion_kernel(LaunchArgs a) {
-  using Rec = Recursion<Fld, N, DL, L, LT>;
-  __shared__ typename Rec::template Lds<BLOCK> lds;
-  const int64_t g = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  const int s = (int)(g % L);
-  const int64_t q0 = g / L;
-  const bool valid = q0 < a.npts;
-  const int64_t q = valid ? q0 : a.npts - 1;  // tail groups recompute the last point
-  uint32_t bad = 0;
-  bool singular = false;
-  typename Fld::S res;
-  typename Fld::E kroot[DL];
+// One point's result: the amplitude by the group's first lane, or the root
+// current by all of them, and the status.
+template <class Fld, int DL, int L>
+__device__ __forceinline__ void store_point(const LaunchArgs& a, int64_t q, bool valid, int s, uint32_t bad,
+                                            bool singular, typename Fld::S res, typename Fld::E (&kroot)[DL]) {
   if constexpr (Fld::exact) {
-    Fld F(a.fp, s);
-    if (a.metric != 0) Rec::template run<BLOCK, MetricAlt>(F, a, q, s, bad, singular, res, kroot, &lds);
-    else Rec::template run<BLOCK, MetricMM>(F, a, q, s, bad, singular, res, kroot, &lds);
     if constexpr (L > 1)
       bad = group_sum<L>(bad, [](uint32_t x, uint32_t y) { return x > y ? x : y; },
                          [](auto ctrl, uint32_t v) { return dpp_u32<decltype(ctrl)::value>(v); });
@@ -694,8 +729,6 @@ void bg_recursion_kernel(LaunchArgs a) {
       if (a.status) a.status[q] = st;
     }
   } else {
-    Fld F(s);
-    Rec::template run<BLOCK, MetricRT>(F, a, q, s, bad, singular, res, kroot, &lds);
     if (a.cur) {
       if (valid) {
 #pragma unroll
@@ -724,6 +757,89 @@ void bg_recursion_kernel(LaunchArgs a) {
       static_cast<double2*>(a.out)[q] = o;
       if (a.status) a.status[q] = singular ? PT_SINGULAR : PT_OK;
     }
+  }
+}
+
+// W = minimum waves per SIMD the register allocation must allow (1: the whole
+// register file for one wave; 2: at most 256 registers per lane).
+template <class Fld, int N, int DL, int L, int BLOCK, bool LT, int W>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W)))
+void bg_recursion_kernel(LaunchArgs a) {
+  using Rec = Recursion<Fld, N, DL, L, LT>;
+  __shared__ typename Rec::template Lds<BLOCK> lds;
+  const int64_t g = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  const int s = (int)(g % L);
+  const int64_t q0 = g / L;
+  const bool valid = q0 < a.npts;
+  const int64_t q = valid ? q0 : a.npts - 1;  // tail groups recompute the last point
+  uint32_t bad = 0;
+  bool singular = false;
+  typename Fld::S res;
+  typename Fld::E kroot[DL];
+  if constexpr (Fld::exact) {
+    Fld F(a.fp, s);
+    if (a.metric != 0) Rec::template run<BLOCK, MetricAlt>(F, a, q, s, bad, singular, res, kroot, &lds);
+    else Rec::template run<BLOCK, MetricMM>(F, a, q, s, bad, singular, res, kroot, &lds);
+  } else {
+    Fld F(s);
+    Rec::template run<BLOCK, MetricRT>(F, a, q, s, bad, singular, res, kroot, &lds);
+  }
+  store_point<Fld, DL, L>(a, q, valid, s, bad, singular, res, kroot);
+}
+
+// ---------------------------------------------------------------------------
+// streaming form: resident blocks, each point's inputs read one point ahead
+// ---------------------------------------------------------------------------
+// A complex kernel whose table takes more than half of the register file runs
+// one wave per SIMD, so nothing covers a wave's start: at n = 8, d = 4 (2^20
+// points) of 44.6 k cycles per wave and SIMD 2.6 k had no wave and 4.6 k waited
+// for loads.  Here one block per CU stays and takes every gridDim-th block of
+// points, and a point's inputs are read while the point before it is computed,
+// into registers that the recursion leaves free (accumulation registers, which
+// loads can write directly).  2^20 points of n = 8, d = 4: 1.43 M -> 1.26 M
+// cycles, 620 -> 591 us (at a lower clock: FP64 at this rate is power limited);
+// n = 7 d = 4 and d = 8 203 -> 187 us and 188 -> 173 us (5 and 2 * 10^5
+// points), n = 6 d = 6 160 -> 146 us, n = 5 d = 8 134 -> 122 us.
+//
+// Where it pays: the table and the sums of the last column take over 200 of
+// the 512 registers (one wave per SIMD either way; at two or more, n = 5 d = 6
+// is 1.2 times slower with it), they fit 400 with the inputs of the next point
+// (beyond, spills: n = 5 d = 10, at 420, 1.5 times slower), and a lane holds
+// several components (one per lane on four lanes: 0.9 to 1.0 times the speed
+// at n = 10 to 12).  Z_p kernels have no such form: in a loop over points the
+// compiler multiplies with 64-bit sequences, n = 9 d = 8 112 -> 129 us.
+template <class Fld, int N, int DL, bool LT>
+constexpr bool stream_pays() {
+  constexpr int vec = DL * (int)sizeof(typename Fld::E) / 4;  // registers of one vector's part
+  constexpr int held = vec * (Ranges<N>::ncur + N), ahead = vec * 2 * N;
+  return !Fld::exact && LT && DL >= 2 && held > 200 && held + ahead <= 400;
+}
+
+template <class Fld, int N, int DL, int L, int BLOCK, bool LT, int W>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W)))
+void bg_recursion_stream_kernel(LaunchArgs a) {
+  using Rec = Recursion<Fld, N, DL, L, LT>;
+  __shared__ typename Rec::template Lds<BLOCK> lds;
+  constexpr int PB = BLOCK / L;  // points of a block at a time
+  const int s = (int)(threadIdx.x % L), pl = (int)(threadIdx.x / L);
+  Fld F(s);
+  const int64_t step = (int64_t)gridDim.x * PB;
+  int64_t b0 = (int64_t)blockIdx.x * PB;
+  typename Rec::Raw raw;
+  raw.read(a, b0 + pl < a.npts ? b0 + pl : a.npts - 1, s * DL);
+  for (; b0 < a.npts; b0 += step) {
+    const int64_t q0 = b0 + pl;
+    const bool valid = q0 < a.npts;
+    const int64_t q = valid ? q0 : a.npts - 1;  // tail groups recompute the last point
+    uint32_t bad = 0;
+    bool singular = false;
+    typename Fld::S res;
+    typename Fld::E kroot[DL];
+    // past the end a group reads its own point again: one point read by every
+    // group would keep a single L2 channel busy for microseconds
+    Rec::template run<BLOCK, MetricRT, true>(F, a, q, s, bad, singular, res, kroot, &lds, &raw,
+                                             q0 + step < a.npts ? q0 + step : q);
+    store_point<Fld, DL, L>(a, q, valid, s, bad, singular, res, kroot);
   }
 }
 

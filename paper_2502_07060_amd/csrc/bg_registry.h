@@ -33,6 +33,9 @@ struct Variant {
   const void* fn_sc = nullptr;
   // lane-group kernel: its persistent work-queue form (bg_wide_queue_kernel)
   const void* fn_queue = nullptr;
+  // register kernel: its streaming form (bg_recursion_stream_kernel), for
+  // launches of more than two rounds of resident blocks
+  const void* fn_stream = nullptr;
 };
 
 // |2^32 mod p| (balanced) <= 2^22: the small-fold-constant schedule applies
@@ -91,6 +94,15 @@ unsigned wide_lds_bytes(int N) {
   return Layout::offsets(N).total;
 }
 
+// the streaming form of a register kernel, null where it has none
+template <class Fld, int N, int DL, int L, bool LT, int W>
+const void* stream_form() {
+  if constexpr (stream_pays<Fld, N, DL, LT>())
+    return reinterpret_cast<const void*>(&bg_recursion_stream_kernel<Fld, N, DL, L, 256, LT, W>);
+  else
+    return nullptr;
+}
+
 }  // namespace bg
 
 #define BG_CAT2(a, b) a##b
@@ -103,7 +115,8 @@ unsigned wide_lds_bytes(int N) {
   template __global__ void bg_recursion_kernel<FLD<DL_, L_>, N_, DL_, L_, 256, LT_, W_>(LaunchArgs);   \
   static Registrar BG_CAT(reg_, __COUNTER__)(Variant{                                                   \
       FIELDTAG, N_, DL_, L_, 256, false, LT_, W_,                                                       \
-      reinterpret_cast<const void*>(&bg_recursion_kernel<FLD<DL_, L_>, N_, DL_, L_, 256, LT_, W_>)});   \
+      reinterpret_cast<const void*>(&bg_recursion_kernel<FLD<DL_, L_>, N_, DL_, L_, 256, LT_, W_>),     \
+      nullptr, false, 1, nullptr, nullptr, stream_form<FLD<DL_, L_>, N_, DL_, L_, LT_, W_>()});         \
   }
 
 // the same for Z_p: both reduction schedules, selected per launch by the prime
