@@ -119,6 +119,7 @@ def generated_units():
     for field, dm, G, pad, lc in WIDE_VARIANTS:
         tag, cls = FIELD[field]
         units.setdefault(f"inst_{field}_wide_g{G}{'_pad' if pad else ''}{'_s' + str(lc) if lc > 1 else ''}", []).append(
+            f"BG_REGISTER_WIDE_FP({dm}, {G}, {'true' if pad else 'false'}, {lc})" if field == "fp" else
             f"BG_REGISTER_WIDE({tag}, {cls}, {dm}, {G}, {'true' if pad else 'false'}, {lc})")
     out = {}
     for name, lines in units.items():

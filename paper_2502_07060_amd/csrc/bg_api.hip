@@ -390,7 +390,7 @@ int prepare(int field, int n, int d, int64_t npts, int64_t ld, const void* momen
   if (shmem > 65536) {
     static std::mutex mu;
     std::lock_guard<std::mutex> lk(mu);
-    (void)hipFuncSetAttribute(v->fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    (void)hipFuncSetAttribute(spec.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   }
   const int64_t blocks = (npts + P - 1) / P;
   if (blocks > 0x7FFFFFFF) return BG_EINVAL;

@@ -263,6 +263,8 @@ struct Recursion {
   using R = Ranges<N>;
   static constexpr int NCUR = R::ncur;   // non-root currents
   static constexpr int NP = R::nprop;    // propagators
+  // F_p schedule for small fold constants (FpField)
+  static constexpr bool kSmallFold = []() { if constexpr (Fld::exact) return Fld::kSC; else return false; }();
 
   // LDS footprint of the tables when LT: scalars per point, vector slots per lane
   static constexpr int kScalars = Fld::exact ? 2 * NP + NCUR : NP;

@@ -28,8 +28,9 @@ struct Variant {
   unsigned (*lds_per_point)(int N) = nullptr;  // runtime-n kernels: LDS bytes per point
   bool padded = false;  // lane-group kernel whose table rows are padded to an odd number of 16-byte units
   int split = 1;        // lane-group kernel: lanes per work item (DL / split components each)
-  // Z_p register kernel compiled for the small-fold-constant schedule (primes
-  // with |2^32 mod p| <= 2^22); the launch takes it instead of fn for those
+  // Z_p register or lane-group kernel compiled for the small-fold-constant
+  // schedule (primes with |2^32 mod p| <= 2^22); the launch takes it instead of
+  // fn for those
   const void* fn_sc = nullptr;
   // lane-group kernel: its persistent work-queue form (bg_wide_queue_kernel)
   const void* fn_queue = nullptr;
@@ -152,4 +153,21 @@ const void* stream_form() {
       reinterpret_cast<const void*>(&bg_wide_kernel<FLD<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>),               \
       &wide_lds_bytes<WideLayout<FLD<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>>, PAD_, LC_, nullptr,              \
       reinterpret_cast<const void*>(&bg_wide_queue_kernel<FLD<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>)});       \
+  }
+
+// the same for Z_p: both reduction schedules, selected per launch by the prime
+// (the work-queue form, whose groups may have primes of either kind, takes the
+// general one)
+#define BG_REGISTER_WIDE_FP(DMAX_, G_, PAD_, LC_)                                                           \
+  namespace bg {                                                                                            \
+  template __global__ void bg_wide_kernel<FpField<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>(LaunchArgs, int);     \
+  template __global__ void bg_wide_kernel<FpField<DMAX_ / LC_, LC_, true>, DMAX_, G_, PAD_>(LaunchArgs, int); \
+  template __global__ void bg_wide_queue_kernel<FpField<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>(                \
+      const QueueGroup*, int, uint32_t, uint32_t*);                                                         \
+  static Registrar BG_CAT(reg_, __COUNTER__)(Variant{                                                       \
+      FIELD_FP, 0, DMAX_, G_ * LC_, 0, true, true, 1,                                                       \
+      reinterpret_cast<const void*>(&bg_wide_kernel<FpField<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>),           \
+      &wide_lds_bytes<WideLayout<FpField<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>>, PAD_, LC_,                   \
+      reinterpret_cast<const void*>(&bg_wide_kernel<FpField<DMAX_ / LC_, LC_, true>, DMAX_, G_, PAD_>),     \
+      reinterpret_cast<const void*>(&bg_wide_queue_kernel<FpField<DMAX_ / LC_, LC_>, DMAX_, G_, PAD_>)});   \
   }

@@ -37,6 +37,14 @@
 // F_p propagator inverses: each item inverts its share of the denominators
 // with one batched inversion and one Fermat power.
 //
+// F_p schedules, as in the register kernel and bounded the same way
+// (FpField): for small fold constants the scalars stop at one 32-bit REDC step
+// and a fold empties an accumulator, so a current takes seven splits between
+// folds instead of five and the sums over a range's items take none.  VALU
+// issue bounds these kernels (0.9 of the cycles): 92609 points of n = 12, d = 8
+// 416 -> 392 us, 13168 of n = 13, d = 10 146 -> 126 us, 11460 of n = 14, d = 10
+// 167 -> 152 us, 28911 of n = 14, d = 4 177 -> 165 us.
+//
 // Component split.  With Fld = C128Field<DL, LC> or FpField<DL, LC>, LC > 1,
 // each work item belongs to LC adjacent lanes that hold DL = DMAX / LC
 // components each and sum dot products over DPP: LC times the lanes per point
@@ -140,6 +148,11 @@ struct WideRecursion {
   static constexpr int LC = Fld::kL;    // lanes per work item
   using Rec = Recursion<Fld, 2, DL, LC>;  // scalar helpers
   static constexpr bool kFp = Fld::exact;
+  // F_p, small fold constant: scalars that only multiply vectors take one
+  // 32-bit REDC step and carry 2^32 (FpField::finish_dot), as in the register
+  // kernel, and a folded accumulator is one unit of 511, so sums over a
+  // range's items need no folds of their own
+  static constexpr bool kSC = Rec::kSmallFold;
   // per-item sum of the -(J_A . J_B) of its cuts: F_p an int64 sum of
   // products with 1/2, complex the plain sum
   using NDS = std::conditional_t<kFp, int64_t, S>;
@@ -325,7 +338,7 @@ struct WideRecursion {
         E Pp[DL], e[DL];
         lazyP(F, l, l, Pp);
         loadJ(rid(l, l), e);
-        nct[rid(l, l)] = F.template ndot<4>(Pp, e);
+        nct[rid(l, l)] = F.template ndot<4, kSC>(Pp, e);
       }
     }
   }
@@ -384,10 +397,12 @@ struct WideRecursion {
       }
       if (any) {
         // products of three instructions in the Montgomery domain of 2^32: y's
-        // inverse there is R/y, and the factor -2 R 2^-32 turns -R/P^2 R^-1 into
-        // 2/P^2 with the extra 2^-32 that finish_mul32 expects
+        // inverse there is R/y, and the factor 2 R 2^-32 turns -R/P^2 R^-1 into
+        // -2/P^2 (K holds -K') with the extra 2^-32 that finish_mul32 expects.
+        // Small fold constant: the factor 2, 2^64 less, for the 2^32 that K
+        // carries and the last 32-bit REDC step there
         int32_t t = fp_pow32(acc, (uint32_t)(F.k.p - 2), F.k);
-        t = fp_mul32(t, -F.k.two, F.k);
+        t = fp_mul32(t, kSC ? 2 : F.k.two, F.k);
         int last = g;
         while (last + G < np) last += G;
         for (int r = last; r >= g; r -= G) {
@@ -402,7 +417,8 @@ struct WideRecursion {
 
   // ---- one three-gluon cut: contributions of cut c to K'(S), S = [i..j] ---
   // the split [i..c] | [c+1..j] and the adjacent-pair terms of the four-gluon
-  // vertex that involve this cut.  F_p: Pp holds P_S as unreduced
+  // vertex that involve this cut.  F_p: K accumulates -K', whose terms take the
+  // negated dot products as they come, Pp holds P_S as unreduced
   // differences, nDs accumulates -(J_A.J_B) / 2 as an int64 sum of products;
   // complex: PA, PB are the primed P_A, P_B (Pp unused), nDs sums -(J_A.J_B).
   __device__ void cut3(const Fld& F, int i, int j, int c, const E (&Pp)[DL], const E (&PA)[DL],
@@ -411,19 +427,23 @@ struct WideRecursion {
     const int ra = rid(i, c), rb = rid(c + 1, j);
     loadJ(ra, JA);
     loadJ(rb, JB);
-    const S nDm = F.ndot_u(JA, JB);  // -(J_A . J_B)
+    const S nDm = F.template ndot_u<kSC>(JA, JB);  // -(J_A . J_B)
     if constexpr (kFp) {
       // the adjacent-pair terms -Dh(A) J_B and -Dh(B) J_A join the scalars
       // of the J_B and J_A axpys: -Dh (balanced, zero for a single leg),
-      // lifted by R, enters each dot product's accumulator before its REDC
+      // lifted by R (small fold constant: by 2^32), enters each dot product's
+      // accumulator before its REDC
+      constexpr int kLift = kSC ? 3 : 2;
       E Qt[DL];
       loadM(c + 1, Qt);
-      const S nc2 = F.template ndot_sub2<4, 2, false, 2>(Pp, JA, nct[ra], nDht[ra]);            // -(P_B.J_A) + Dh(A)
-      const S nc3 = F.template ndot_sub2<4, 2, false, 2>(Pp, JB, nct[rb], F.sneg(nDht[rb]));   // -(P_A.J_B) - Dh(B)
-      F.axpy(K, F.sneg(nDm), Qt);
-      F.axpy(K, F.sneg(nc2), JB);
-      F.axpy(K, nc3, JA);
-      nDs = fp_fold(mad64(nDm, F.k.inv2, nDs), F.k);
+      const S nc2 = F.template ndot_sub2<4, kLift, kSC, kLift>(Pp, JA, nct[ra], nDht[ra]);  // -(P_B.J_A) + Dh(A)
+      const S nc3 =
+          F.template ndot_sub2<4, kLift, kSC, kLift>(Pp, JB, nct[rb], F.sneg(nDht[rb]));  // -(P_A.J_B) - Dh(B)
+      F.axpy(K, nDm, Qt);
+      F.axpy(K, nc2, JB);
+      F.axpy(K, F.sneg(nc3), JA);
+      nDs = mad64(nDm, F.k.inv2, nDs);  // two cuts fit; small fold constant: 132 units
+      if constexpr (!kSC) nDs = fp_fold(nDs, F.k);
     } else {
       // the adjacent-pair terms: the lanes of the item start their partial
       // dot products from their share of -Dh (the table holds -Dh / LC, zero
@@ -473,10 +493,10 @@ struct WideRecursion {
       E JM[DL], JC[DL];
       load_row(reinterpret_cast<const E*>(base + am), JM);
       load_row(reinterpret_cast<const E*>(base + ac), JC);
-      const S ne = F.ndot_u(JA, JC);
-      F.axpy(K, F.sneg(ne), JM);
-      if constexpr (kFp)
-        if (++cnt == 5) { F.fold(K); cnt = 0; }
+      const S ne = F.template ndot_u<kSC>(JA, JC);
+      F.axpy(K, kFp ? ne : F.sneg(ne), JM);
+      if constexpr (kFp)  // products since the last fold: 4 + 5 2 of 15, or 1 + 7 66 of 511
+        if (++cnt == (kSC ? 7 : 5)) { F.fold(K); cnt = 0; }
       am += dm;
       dm -= kRow;
       ac += dc;
@@ -491,7 +511,7 @@ struct WideRecursion {
   __device__ __forceinline__ void xor_step(const Fld& F, A (&K)[DL], NDS& nDs) const {
 #pragma unroll
     for (int c = 0; c < DL; ++c) K[c] = add_acc(F, K[c], lane_xor<ST>(K[c]));
-    if constexpr (kFp) nDs = fp_fold(nDs + lane_xor<ST>(nDs), F.k);
+    if constexpr (kFp) nDs = add_acc(F, nDs, lane_xor<ST>(nDs));
     else nDs = cadd(nDs, lane_xor<ST>(nDs));
   }
   __device__ __forceinline__ void range_sum(const Fld& F, A (&K)[DL], NDS& nDs, int per) const {
@@ -562,6 +582,7 @@ struct WideRecursion {
           }
           cut4(F, i, j, c1, c2, K);
         }
+        if constexpr (kSC) nDs = fp_fold(nDs, F.k);
         if constexpr (kFp) {
           if (m < N) {
             scalar_sum<LC>(F, nDs, lg);
@@ -574,9 +595,9 @@ struct WideRecursion {
           const int id = rid(r, r + m - 1);
           S nDhS;
           if constexpr (kFp) {
-            nDhS = fp_redc2(fp_fold(nDs, F.k), F.k);  // the cuts' sums already carry the factor 1/2
-            // -Dh(S) (Q_i + Q_{j+1})
-            F.axpy(K, nDhS, QQ);
+            nDhS = range_dh(F, nDs);
+            // Dh(S) (Q_i + Q_{j+1})
+            F.axpy(K, F.sneg(nDhS), QQ);
             F.fold(K);
           } else {
             constexpr double kPart = 0.5 / Fld::kL;  // -Dh(S) / LC, the lanes' share
@@ -588,11 +609,9 @@ struct WideRecursion {
             E Jn[DL];
 #pragma unroll
             for (int c = 0; c < DL; ++c) {
-              if constexpr (kFp) Jn[c] = F.finish_mul32(K[c], inv2);
-              else Jn[c] = F.mul(F.finish(K[c]), inv2);
+              Jn[c] = F.mul(F.finish(K[c]), inv2);
               Jat(id, co + c) = Jn[c];
             }
-            if constexpr (kFp) nct[id] = F.template ndot<4>(Pp, Jn);
           } else {
             E Kf[DL], en[DL];
 #pragma unroll
@@ -628,7 +647,7 @@ struct WideRecursion {
   __device__ __forceinline__ void scalar_sum(const Fld& F, int64_t& x, int lg) const {
     if constexpr (ST <= 32) {
       if (lg > 0) {
-        x = fp_fold(x + lane_xor<ST>(x), F.k);
+        x = add_acc(F, x, lane_xor<ST>(x));
         scalar_sum<ST * 2>(F, x, lg - 1);
       }
     }
@@ -673,13 +692,13 @@ struct WideRecursion {
 #pragma unroll
     for (int q = 0; q < DN; ++q) K[q] = V[q];
     rest_sum<ST, DN>(F, K, lg);
-    const S nDhS = fp_redc2(fp_fold(nDs, F.k), F.k);  // the cuts' sums already carry the factor 1/2
+    const S nDhS = range_dh(F, nDs), Dh = F.sneg(nDhS);
     A t = 0;
     int uu = 0;
 #pragma unroll
     for (int q = 0; q < DN; ++q) {
-      // -Dh(S) (Q_i + Q_{j+1}), then J = K' 2/P_S^2
-      const E Jn = F.finish_mul32(fp_fold(mad64(nDhS, Qv[q], K[q]), F.k), inv2);
+      // Dh(S) (Q_i + Q_{j+1}), then J = -K' (-2/P_S^2)
+      const E Jn = F.finish_mul32(mad64(Dh, Qv[q], K[q]), inv2);
       Jat(id, co + cb + q * cs) = Jn;
       // P_S . J_S over this slot's components (an unreduced difference times
       // a balanced value: the dot products' UX = 4 class)
@@ -692,17 +711,25 @@ struct WideRecursion {
     }
     t = fp_fold(t, F.k);
     scalar_sum<LC>(F, t, lgall - lg);  // over the slots whose components differ
-    const S nc = F.template finish_dot<false>(t, Fld::kFoldU);
+    const S nc = F.template finish_dot<kSC>(t, kSumU);
     if (first) {
       nct[id] = nc;
       nDht[id] = nDhS;
     }
   }
 
-  // K + partial (F_p: both below 2^61 + 2^32 after their folds, refolded)
+  // x + y over a range's items.  F_p: both below 2^61 + 2^32 after their folds,
+  // refolded; small fold constant: at most 32 folded values of one unit each
+  static constexpr int kSumU = []() { if constexpr (kSC) return 32; else if constexpr (kFp) return Fld::kFoldU; else return 0; }();
   __device__ __forceinline__ static A add_acc(const Fld& F, A x, A y) {
-    if constexpr (kFp) return fp_fold(x + y, F.k);
+    if constexpr (kSC) return x + y;
+    else if constexpr (kFp) return fp_fold(x + y, F.k);
     else return cadd(x, y);
+  }
+  // F_p: -Dh(S) from the range's sum, which already carries the factor 1/2
+  __device__ __forceinline__ static S range_dh(const Fld& F, int64_t nDs) {
+    if constexpr (kSC) return fp_redc2(nDs, F.k);  // 32 units of 256
+    else return fp_redc2(fp_fold(nDs, F.k), F.k);
   }
 };
 
@@ -726,15 +753,16 @@ __device__ __forceinline__ void wide_point(const LaunchArgs& a, int N, char* lds
       const unsigned fl = *W.flags;
       const uint8_t st = (fl & 1u) ? PT_BADRESIDUE : ((fl & 2u) ? PT_SINGULAR : PT_OK);
       if (a.cur) {
-        // root current K = 2 K', kroot scaled by R^-3: one product with R^3
+        // root current K = 2 K', kroot = -K' scaled by R^-3 (small fold constant:
+        // and by the 2^32 of its scalars): one product with R^3
 #pragma unroll
         for (int c = 0; c < WR::DL; ++c) {
           const int mu = W.co + c;
           if (mu < a.d) {
             uint32_t v = 0xFFFFFFFFu;
             if (st == PT_OK) {
-              const int32_t m = fp_mul(kroot[c], a.fp.r3, a.fp);
-              v = fp_to_canonical(fp_add(m, m, a.fp), a.fp);
+              const int32_t m = fp_mul(kroot[c], WR::kSC ? a.fp.r3s : a.fp.r3, a.fp);
+              v = fp_to_canonical(fp_sub(0, fp_add(m, m, a.fp), a.fp), a.fp);
             }
             static_cast<uint32_t*>(a.cur)[(int64_t)mu * a.ld + q] = v;
           }
@@ -742,9 +770,8 @@ __device__ __forceinline__ void wide_point(const LaunchArgs& a, int N, char* lds
       } else if (W.s == 0) {
         uint32_t outv = 0xFFFFFFFFu;
         if (st == PT_OK) {
-          int32_t m = fp_mul(res, a.fp.r4, a.fp);
-          m = fp_sub(0, fp_add(m, m, a.fp), a.fp);
-          outv = fp_to_canonical(m, a.fp);
+          const int32_t m = fp_mul(res, WR::kSC ? a.fp.r4s : a.fp.r4, a.fp);
+          outv = fp_to_canonical(fp_add(m, m, a.fp), a.fp);
         }
         static_cast<uint32_t*>(a.out)[q] = outv;
       }
