@@ -178,8 +178,10 @@ constexpr int64_t kManyPts = 65536;      // several waves of any register kernel
 // for them, 16 below (n = 12, d = 6, 3 10^4 points: 281 against 371); d = 7, 8
 // with four lanes per item and 16 items up to n = 13 (n = 12: 393 against 450),
 // at n = 14 two lanes with padded rows (687 against 836 unpadded, whose rows
-// share banks), as at n = 13, d = 9, 10 (729 against 788).  For few points 64 lanes per point (n = 10, d = 4, 1000
-// points: 17 against 20 with 32).
+// share banks), as at n = 13, d = 9, 10 (729 against 788) and at n = 11,
+// d = 5, 6 (8192 points: 66 against 76).  For few points 64 lanes per point
+// (n = 10, d = 4, 1000 points: 17 against 20 with 32), at n = 8, d = 5, 6 half
+// as many (1500 points: 15.2 against 16.9 with 64).
 static const Variant* lane_group_c128(int n, int d, int64_t npts) {
   const bool few = npts <= kGroupPts / 2;
   if (d <= 4) {
@@ -187,8 +189,8 @@ static const Variant* lane_group_c128(int n, int d, int64_t npts) {
     return lane_group_variant(FIELD_C128, 4, n >= 13 ? 32 : 16, 2, n < 13);
   }
   if (d <= 6) {
-    if (few && n <= 11) return lane_group_variant(FIELD_C128, 8, 16, 4, true);
-    return lane_group_variant(FIELD_C128, 6, few || n >= 13 ? 32 : 16, 2, false);
+    if (n <= 8 ? npts <= kGroupPts / 4 : few && n <= 11) return lane_group_variant(FIELD_C128, 8, 16, 4, true);
+    return lane_group_variant(FIELD_C128, 6, (few && n > 8) || n >= 13 ? 32 : 16, 2, n == 11);
   }
   if (d <= 8) {
     if (n >= 14 || (n == 13 && npts <= kFourLanePts)) return lane_group_variant(FIELD_C128, 8, 32, 2, true);
@@ -200,9 +202,10 @@ static const Variant* lane_group_c128(int n, int d, int64_t npts) {
 
 // Lane-group kernels over Z_p: one lane per item and 16 items per point for
 // many points (n = 12, d = 8, 10^5 points, unpadded rows: 461 against 534
-// padded), 32 at n = 14 (d = 6: 778 against 827); two lanes per item for few
-// points (n = 11, d = 8, 1000 points: 25 against 46 with 16 lanes per point)
-// and for d = 9, 10 at n = 12, 13 (222 against 231 at 3 10^4 points).
+// padded), 32 at n = 14 (d = 6: 778 against 827), where d = 7, 8 takes padded
+// rows (2 10^4 points: 178 against 198); two lanes per item for few points
+// (n = 11, d = 8, 1000 points: 25 against 46 with 16 lanes per point) and for
+// d = 9, 10 from n = 12 on (n = 14, 10^5 points: 1048 against 1093).
 static const Variant* lane_group_fp(int n, int d, int64_t npts) {
   if (npts <= kGroupPts / 2) {
     if (d <= 4) return lane_group_variant(FIELD_FP, 4, 32, 1, false);
@@ -214,25 +217,24 @@ static const Variant* lane_group_fp(int n, int d, int64_t npts) {
     if (d <= 6 && n >= 13) return lane_group_variant(FIELD_FP, 6, 32, 1, false);
     return lane_group_variant(FIELD_FP, 8, d > 6 && n >= 13 ? 32 : 16, 2, false);
   }
-  if (d > 8)
-    return n >= 14 ? lane_group_variant(FIELD_FP, 10, 32, 1, false)
-                   : lane_group_variant(FIELD_FP, 10, 16, n >= 12 ? 2 : 1, false);
+  if (d > 8) return lane_group_variant(FIELD_FP, 10, 16, n >= 12 ? 2 : 1, false);
   const int dmax = d <= 4 ? 4 : d <= 6 ? 6 : 8;
   const bool items32 = n >= 14 && (dmax > 4 || npts <= kManyPts / 2);
-  return lane_group_variant(FIELD_FP, dmax, items32 ? 32 : 16, 1, false);
+  return lane_group_variant(FIELD_FP, dmax, items32 ? 32 : 16, 1, items32 && dmax == 8);
 }
 
 // Register kernels over C.  Four lanes per point for d = 7, 8 (two components
 // a lane; n = 8, 10^5 points: 158 against 265 with two lanes, whose currents
-// spill), for d = 9, 10 except n = 4 and 6 (n = 7: 141 against 225) and from
-// n = 9 on for d > 4 (n = 9, d = 6: 242 against 266); else two (n = 8, d = 4,
+// spill), for d = 9, 10 from n = 7 on (n = 7: 141 against 225) and at n = 5, 6
+// for many points (n = 6, 2 10^5 points: 147 against 169) and from n = 9 on for
+// d > 4 (n = 9, d = 6: 242 against 266); else two (n = 8, d = 4,
 // 5 10^5 points: 329 against 366).
 static const Variant* register_c128(int n, int d, int64_t npts) {
   const Variant* four = register_variant(FIELD_C128, n, d, 4);
   const Variant* two = register_variant(FIELD_C128, n, d, 2);
   if (!four || !two) return four ? four : two;
   if (npts <= kFourLanePts || n >= 11) return four;
-  if (d >= 9) return (n == 5 && npts >= kManyPts) || n >= 7 ? four : two;
+  if (d >= 9) return (n >= 5 && npts >= kManyPts) || n >= 7 ? four : two;
   if (d >= 7) return n >= 7 || npts >= kManyPts ? four : two;
   return d > 4 && n >= 9 ? four : two;
 }
@@ -241,21 +243,15 @@ static const Variant* register_c128(int n, int d, int64_t npts) {
 // fewer instructions) for many points of d <= 6 (n = 6, d = 6, 5 10^5 points:
 // 76 against 93), at n = 7, 8 with d = 5, 6 only up to two waves per SIMD
 // (n = 8, d = 6, 10^5 points: 50 against 52; 2 10^5: 98 against 87).  Four for
-// few points, for d = 7, 8 at n <= 5 up to twice as many (3 10^4 points: 7.0
-// against 8.1) and for d = 9, 10 at n = 5, 6 (10^5 points: 33 against 42, 49
-// against 60).  Else two, at n = 7, d = 7, 8 with five components a lane (10^5
-// points: 56 against 67 with four).
+// few points (n = 6, d = 10, 10^4 points: 10.0 against 11.6 with two), except
+// at n = 4, d = 9, 10 (6.8 against 6.1).  Else two (n = 6, d = 10, 5 10^4
+// points: 18.5 against 26 with four).
 static const Variant* register_fp(int n, int d, int64_t npts) {
   const Variant* four = register_variant(FIELD_FP, n, d, 4);
   const Variant* one = register_variant(FIELD_FP, n, d, 1);
   const Variant* two = register_variant(FIELD_FP, n, d, 2);
-  if (four && npts <= kFourLanePts && (d >= 7 || (d >= 5 && n <= 6))) return four;
-  if (four && (d >= 9 ? n == 5 || n == 6 : d >= 7 && n <= 5 && npts <= 2 * kFourLanePts)) return four;
+  if (four && npts <= kFourLanePts && (d >= 9 ? n >= 5 : d >= 7 || (d >= 5 && n <= 6))) return four;
   if (one && npts >= kManyPts && (n <= 6 || d <= 4 || npts <= 2 * kManyPts)) return one;
-  if (two && n == 7 && (d == 7 || d == 8) && npts > kFourLanePts) {
-    const Variant* five = register_variant(FIELD_FP, n, 10, 2);
-    if (five) return five;
-  }
   return two ? two : (one ? one : four);
 }
 
@@ -265,9 +261,15 @@ const Variant* default_variant(int field, int n, int d, int64_t npts) {
     // lane-group for few points from n = 7 (d > 4; n = 8, d = 8, 1000 points:
     // 14 against 49 on two lanes) and where no register kernel is compiled
     // (n >= 13; n = 12, d > 4; n >= 9, d > 8); at n = 11, d = 8, 10^5 points
-    // the register kernel takes 682, the best lane-group one 840
-    const int64_t few = n >= 9            ? kGroupPts
-                        : n == 8          ? (d > 8 ? kGroupPts : d > 4 ? kGroupPts / 2 : kGroupPts / 4)
+    // the register kernel takes 682, the best lane-group one 840.  For d = 5, 6
+    // the lane-group kernels, three waves per SIMD there, hold out longer (n = 11,
+    // d = 6: 66 against 97 at 8192 points, 94 against 100 at 12000; n = 10: 35
+    // against 53 at 5000, n = 8: 20 against 22 at 4096)
+    const bool mid = d == 5 || d == 6;
+    const int64_t few = mid && n == 11    ? 3 * kGroupPts
+                        : mid && n >= 9   ? kGroupPts * 3 / 2
+                        : n >= 9          ? kGroupPts
+                        : n == 8          ? (d > 8 || mid ? kGroupPts : d > 4 ? kGroupPts / 2 : kGroupPts / 4)
                         : n == 7 && d > 4 ? kGroupPts / 4
                                           : 0;
     v = register_c128(n, d, npts);
@@ -276,9 +278,10 @@ const Variant* default_variant(int field, int n, int d, int64_t npts) {
     // lane-group from n = 8 (d > 4) for few points, at n = 11 up to
     // kFourLanePts (d = 6, 10^4 points: 53 against 74), and there for d > 6 at
     // any size (d = 8, 10^5 points: 388 against 620: the register kernel
-    // spills) and for d <= 4 from kManyPts on (10^5 points: 249 against 298)
+    // spills) and for d <= 4 from kManyPts on (10^5 points: 249 against 298); at
+    // n = 10, d <= 4 up to three times kGroupPts (12000 points: 30 against 34)
     const int64_t few = n == 11           ? (d > 6 ? INT64_MAX : kFourLanePts)
-                        : n == 10         ? (d > 6 ? 2 * kGroupPts : kGroupPts)
+                        : n == 10         ? (d > 6 ? 2 * kGroupPts : d <= 4 ? 3 * kGroupPts : kGroupPts)
                         : n == 9          ? kGroupPts
                         : n == 8 && d > 4 ? kGroupPts / 4
                                           : 0;
