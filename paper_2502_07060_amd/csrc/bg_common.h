@@ -89,6 +89,7 @@ constexpr int DPP_QP_1032 = 0xB1;
 constexpr int DPP_QP_2301 = 0x4E;
 constexpr int DPP_ROW_HALF_MIRROR = 0x141;
 constexpr int DPP_ROW_MIRROR = 0x140;
+constexpr int DPP_ROW_ROR_8 = 0x128;  // rotation by half a row of 16: lane XOR 8
 
 template <int L, class T, class Add, class Xchg>
 __device__ __forceinline__ T group_sum(T v, Add add, Xchg xchg) {
