@@ -175,13 +175,13 @@ constexpr int64_t kManyPts = 65536;      // several waves of any register kernel
 
 // Lane-group kernels over C: two lanes per work item (half the components
 // each).  32 items per point at n >= 13, where the long ranges have the cuts
-// for them, 16 below (n = 12, d = 6, 3 10^4 points: 281 against 371); d = 7, 8
-// with four lanes per item and 16 items up to n = 13 (n = 12: 393 against 450),
-// at n = 14 two lanes with padded rows (687 against 836 unpadded, whose rows
-// share banks), as at n = 13, d = 9, 10 (729 against 788) and at n = 11,
-// d = 5, 6 (8192 points: 66 against 76).  For few points 64 lanes per point
-// (n = 10, d = 4, 1000 points: 17 against 20 with 32), at n = 8, d = 5, 6 half
-// as many (1500 points: 15.2 against 16.9 with 64).
+// for them, 16 below (n = 12, d = 6, 3 10^4 points: 269 against 353); d = 7, 8
+// with four lanes per item and 16 items up to n = 13 (n = 12: 372 against 441),
+// at n = 14 two lanes with padded rows (657 against 814 unpadded, whose rows
+// share banks), as at n = 13, d = 9, 10 (703 against 762) and at n = 11,
+// d = 5, 6 (8192 points: 64 against 75).  For few points 64 lanes per point
+// (n = 10, d = 4, 1000 points: 16 against 18 with 32), at n = 8, d = 5, 6 half
+// as many (1500 points: 15.3 against 17.1 with 64).
 static const Variant* lane_group_c128(int n, int d, int64_t npts) {
   const bool few = npts <= kGroupPts / 2;
   if (d <= 4) {
@@ -201,11 +201,11 @@ static const Variant* lane_group_c128(int n, int d, int64_t npts) {
 }
 
 // Lane-group kernels over Z_p: one lane per item and 16 items per point for
-// many points (n = 12, d = 8, 10^5 points, unpadded rows: 461 against 534
-// padded), 32 at n = 14 (d = 6: 778 against 827), where d = 7, 8 takes padded
-// rows (2 10^4 points: 178 against 198); two lanes per item for few points
-// (n = 11, d = 8, 1000 points: 25 against 46 with 16 lanes per point) and for
-// d = 9, 10 from n = 12 on (n = 14, 10^5 points: 1048 against 1093).
+// many points (n = 12, d = 8, 10^5 points, unpadded rows: 417 against 501
+// padded), 32 at n = 14 (d = 6: 676 against 731), where d = 7, 8 takes padded
+// rows (2 10^4 points: 175 against 194); two lanes per item for few points
+// (n = 11, d = 8, 1000 points: 22 against 29 with 16 lanes per point) and for
+// d = 9, 10 from n = 12 on (n = 14, 10^5 points: 1039 against 1070).
 static const Variant* lane_group_fp(int n, int d, int64_t npts) {
   if (npts <= kGroupPts / 2) {
     if (d <= 4) return lane_group_variant(FIELD_FP, 4, 32, 1, false);
@@ -224,11 +224,11 @@ static const Variant* lane_group_fp(int n, int d, int64_t npts) {
 }
 
 // Register kernels over C.  Four lanes per point for d = 7, 8 (two components
-// a lane; n = 8, 10^5 points: 158 against 265 with two lanes, whose currents
-// spill), for d = 9, 10 from n = 7 on (n = 7: 141 against 225) and at n = 5, 6
-// for many points (n = 6, 2 10^5 points: 147 against 169) and from n = 9 on for
-// d > 4 (n = 9, d = 6: 242 against 266); else two (n = 8, d = 4,
-// 5 10^5 points: 329 against 366).
+// a lane; n = 8, 10^5 points: 148 against 274 with two lanes, whose currents
+// spill), for d = 9, 10 from n = 7 on (n = 7: 134 against 230) and at n = 5, 6
+// for many points (n = 6, 2 10^5 points: 148 against 170) and from n = 9 on for
+// d > 4 (n = 9, d = 6: 237 against 266); else two (n = 8, d = 4,
+// 5 10^5 points: 283 against 428).
 static const Variant* register_c128(int n, int d, int64_t npts) {
   const Variant* four = register_variant(FIELD_C128, n, d, 4);
   const Variant* two = register_variant(FIELD_C128, n, d, 2);
@@ -241,11 +241,11 @@ static const Variant* register_c128(int n, int d, int64_t npts) {
 
 // Register kernels over Z_p.  One lane per point (no sums over lanes, 30 %
 // fewer instructions) for many points of d <= 6 (n = 6, d = 6, 5 10^5 points:
-// 76 against 93), at n = 7, 8 with d = 5, 6 only up to two waves per SIMD
-// (n = 8, d = 6, 10^5 points: 50 against 52; 2 10^5: 98 against 87).  Four for
+// 64 against 79), at n = 7, 8 with d = 5, 6 only up to two waves per SIMD
+// (n = 8, d = 6, 10^5 points: 47 against 50; 2 10^5: 93 against 83).  Four for
 // few points (n = 6, d = 10, 10^4 points: 10.0 against 11.6 with two), except
-// at n = 4, d = 9, 10 (6.8 against 6.1).  Else two (n = 6, d = 10, 5 10^4
-// points: 18.5 against 26 with four).
+// at n = 4, d = 9, 10 (6.6 against 6.0).  Else two (n = 6, d = 10, 5 10^4
+// points: 18 against 25 with four).
 static const Variant* register_fp(int n, int d, int64_t npts) {
   const Variant* four = register_variant(FIELD_FP, n, d, 4);
   const Variant* one = register_variant(FIELD_FP, n, d, 1);
@@ -259,11 +259,11 @@ const Variant* default_variant(int field, int n, int d, int64_t npts) {
   const Variant* v = nullptr;
   if (field == FIELD_C128) {
     // lane-group for few points from n = 7 (d > 4; n = 8, d = 8, 1000 points:
-    // 14 against 49 on two lanes) and where no register kernel is compiled
+    // 13 against 50 on two lanes) and where no register kernel is compiled
     // (n >= 13; n = 12, d > 4; n >= 9, d > 8); at n = 11, d = 8, 10^5 points
-    // the register kernel takes 682, the best lane-group one 840.  For d = 5, 6
+    // the register kernel takes 686, the best lane-group one 971.  For d = 5, 6
     // the lane-group kernels, three waves per SIMD there, hold out longer (n = 11,
-    // d = 6: 66 against 97 at 8192 points, 94 against 100 at 12000; n = 10: 35
+    // d = 6: 64 against 96 at 8192 points, 92 against 99 at 12000; n = 10: 35
     // against 53 at 5000, n = 8: 20 against 22 at 4096)
     const bool mid = d == 5 || d == 6;
     const int64_t few = mid && n == 11    ? 3 * kGroupPts
@@ -276,10 +276,10 @@ const Variant* default_variant(int field, int n, int d, int64_t npts) {
     if (!v || npts <= few) v = lane_group_c128(n, d, npts);
   } else {
     // lane-group from n = 8 (d > 4) for few points, at n = 11 up to
-    // kFourLanePts (d = 6, 10^4 points: 53 against 74), and there for d > 6 at
-    // any size (d = 8, 10^5 points: 388 against 620: the register kernel
-    // spills) and for d <= 4 from kManyPts on (10^5 points: 249 against 298); at
-    // n = 10, d <= 4 up to three times kGroupPts (12000 points: 30 against 34)
+    // kFourLanePts (d = 6, 10^4 points: 44 against 49), and there for d > 6 at
+    // any size (d = 8, 10^5 points: 337 against 599: the register kernel
+    // spills) and for d <= 4 from kManyPts on (10^5 points: 201 against 211); at
+    // n = 10, d <= 4 up to three times kGroupPts (12000 points: 29 against 34)
     const int64_t few = n == 11           ? (d > 6 ? INT64_MAX : kFourLanePts)
                         : n == 10         ? (d > 6 ? 2 * kGroupPts : d <= 4 ? 3 * kGroupPts : kGroupPts)
                         : n == 9          ? kGroupPts
