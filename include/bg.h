@@ -52,9 +52,9 @@
  * The compute entry points allocate no device memory and are thread safe.
  *
  * Kernels.  A call runs the kernel pinned for its (field, n, d) (see
- * bg_select_variant), else a default for (field, n, d, npts): few points take
- * more lanes each.  Over Z_p every kernel gives the same residues; over C two
- * kernels differ by rounding, so results are bit-identical for equal npts.
+ * bg_select_variant), else a default: over C one for each (n, d), so that a
+ * point has the same bits in any call, whatever its npts; over Z_p, where every
+ * kernel gives the same residues, one for (n, d, npts).
  */
 #ifndef BG_MI355X_H
 #define BG_MI355X_H
@@ -396,8 +396,7 @@ int bg_batch_plan_destroy(bg_batch_plan* plan);
  * runs (s = 16 complex, 4 F_p; columns padded to 64 points, parts to 256
  * bytes).  Requests are admitted first come, first served as arena space
  * and launch slots free up; requests waiting for the same (field, n, d, p)
- * (over C also of the same kernel) are merged into one kernel launch over
- * adjacent columns; several launches
+ * are merged into one kernel launch over adjacent columns; several launches
  * are in flight at once on separate streams, their copies overlapping other
  * launches' kernels.  Every point is computed exactly as by
  * bg_amplitudes_c128 / bg_amplitudes_fp computes it in a call of the request's

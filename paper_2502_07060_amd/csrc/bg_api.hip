@@ -158,9 +158,13 @@ static const Variant* lane_group_variant(int field, int dmax, int G, int LC, boo
   return nullptr;
 }
 
-// Kernel choice without a pin, by (field, n, d) and the number of points.
-// Measured on gfx950 with every compiled kernel at n = 4..14, d = 4..10 and 300
-// to 2^19 points; figures are us per launch, this choice against the next one.
+// Kernel choice without a pin.  Over C it goes by (n, d) alone: two kernels sum
+// in different orders, and a point has to come out with the same bits however
+// many points share its launch (a job in chunks, a request merged with others).
+// Over Z_p, where every kernel gives the same residues, it also goes by the
+// number of points.
+// Measured on gfx950 with every compiled kernel at n = 4..14, d = 4..10 and 100
+// to 2^20 points; figures are us per launch, this choice against the next one.
 //
 // A launch takes the longer of one wave's latency and its share of the issue
 // slots.  While the waves of all points fit the chip at once the latency
@@ -173,31 +177,20 @@ constexpr int64_t kGroupPts = 4096;      // points whose lane-group waves run at
 constexpr int64_t kFourLanePts = 16384;  // points whose four-lane waves (16 points each) do, one per SIMD
 constexpr int64_t kManyPts = 65536;      // several waves of any register kernel per SIMD
 
-// Lane-group kernels over C: two lanes per work item (half the components
-// each).  32 items per point at n >= 13, where the long ranges have the cuts
-// for them, 16 below (n = 12, d = 6, 3 10^4 points: 269 against 353); d = 7, 8
-// with four lanes per item and 16 items up to n = 13 (n = 12: 372 against 441),
-// at n = 14 two lanes with padded rows (657 against 814 unpadded, whose rows
-// share banks), as at n = 13, d = 9, 10 (703 against 762) and at n = 11,
-// d = 5, 6 (8192 points: 64 against 75).  For few points 64 lanes per point
-// (n = 10, d = 4, 1000 points: 16 against 18 with 32), at n = 8, d = 5, 6 half
-// as many (1500 points: 15.3 against 17.1 with 64).
-static const Variant* lane_group_c128(int n, int d, int64_t npts) {
-  const bool few = npts <= kGroupPts / 2;
-  if (d <= 4) {
-    if (few) return n <= 11 ? lane_group_variant(FIELD_C128, 4, 16, 4, true) : lane_group_variant(FIELD_C128, 4, 32, 2, false);
-    return lane_group_variant(FIELD_C128, 4, n >= 13 ? 32 : 16, 2, n < 13);
-  }
-  if (d <= 6) {
-    if (n <= 8 ? npts <= kGroupPts / 4 : few && n <= 11) return lane_group_variant(FIELD_C128, 8, 16, 4, true);
-    return lane_group_variant(FIELD_C128, 6, (few && n > 8) || n >= 13 ? 32 : 16, 2, n == 11);
-  }
-  if (d <= 8) {
-    if (n >= 14 || (n == 13 && npts <= kFourLanePts)) return lane_group_variant(FIELD_C128, 8, 32, 2, true);
-    return lane_group_variant(FIELD_C128, 8, 16, 4, few);
-  }
-  const bool items32 = n >= 13 || (n == 12 && npts <= kGroupPts) || (n == 11 && few);
-  return lane_group_variant(FIELD_C128, 10, items32 ? 32 : 16, 2, n == 13);
+// Lane-group kernels over C (no register kernel is compiled for n >= 13, for
+// n = 12 with d > 4, n >= 9 with d > 8): two lanes per work item (half the
+// components each).  32 items per point at n >= 13, where the long ranges have
+// the cuts for them, 16 below (n = 12, d = 6, 64000 points: 581 against 732,
+// though 100 points take 30 against 26); d = 7, 8 with four lanes per item and 16
+// items up to n = 13 (n = 12, 64000 points: 773 against 913 with two).  Padded
+// rows at n = 14, d <= 4 (2000 points: 35 against 43 unpadded; 64000: 728 against
+// 710), n = 14, d = 7, 8 (64000: 1374 against 1601) and n = 13, d = 9, 10 (64000:
+// 1469 against 1582).
+static const Variant* lane_group_c128(int n, int d) {
+  if (d <= 4) return lane_group_variant(FIELD_C128, 4, 32, 2, n >= 14);
+  if (d <= 6) return lane_group_variant(FIELD_C128, 6, n >= 13 ? 32 : 16, 2, false);
+  if (d <= 8) return n >= 14 ? lane_group_variant(FIELD_C128, 8, 32, 2, true) : lane_group_variant(FIELD_C128, 8, 16, 4, false);
+  return lane_group_variant(FIELD_C128, 10, n >= 13 ? 32 : 16, 2, n == 13);
 }
 
 // Lane-group kernels over Z_p: one lane per item and 16 items per point for
@@ -223,20 +216,18 @@ static const Variant* lane_group_fp(int n, int d, int64_t npts) {
   return lane_group_variant(FIELD_FP, dmax, items32 ? 32 : 16, 1, items32 && dmax == 8);
 }
 
-// Register kernels over C.  Four lanes per point for d = 7, 8 (two components
-// a lane; n = 8, 10^5 points: 148 against 274 with two lanes, whose currents
-// spill), for d = 9, 10 from n = 7 on (n = 7: 134 against 230) and at n = 5, 6
-// for many points (n = 6, 2 10^5 points: 148 against 170) and from n = 9 on for
-// d > 4 (n = 9, d = 6: 237 against 266); else two (n = 8, d = 4,
-// 5 10^5 points: 283 against 428).
-static const Variant* register_c128(int n, int d, int64_t npts) {
+// Register kernels over C.  Four lanes per point where two would hold too many
+// components to keep the currents in registers: d = 9, 10 from n = 5 on (n = 7,
+// 128000 points: 161 against 245), d = 7, 8 from n = 6 on (n = 8, 128000: 175
+// against 294), d = 5, 6 from n = 9 on (n = 9, 128000: 275 against 277, 1000
+// points 1.5 times faster), any d from n = 11 on; else two (n = 8, d = 4, 512000:
+// 294 against 443).  n = 5, d = 7, 8 stay on two: the four-lane kernel is faster
+// at most sizes (256000: 67 against 70), not at 32000 (11.4 against 10.4).
+static const Variant* register_c128(int n, int d) {
   const Variant* four = register_variant(FIELD_C128, n, d, 4);
   const Variant* two = register_variant(FIELD_C128, n, d, 2);
   if (!four || !two) return four ? four : two;
-  if (npts <= kFourLanePts || n >= 11) return four;
-  if (d >= 9) return (n >= 5 && npts >= kManyPts) || n >= 7 ? four : two;
-  if (d >= 7) return n >= 7 || npts >= kManyPts ? four : two;
-  return d > 4 && n >= 9 ? four : two;
+  return n >= (d >= 9 ? 5 : d >= 7 ? 6 : d >= 5 ? 9 : 11) ? four : two;
 }
 
 // Register kernels over Z_p.  One lane per point (no sums over lanes, 30 %
@@ -258,22 +249,8 @@ static const Variant* register_fp(int n, int d, int64_t npts) {
 const Variant* default_variant(int field, int n, int d, int64_t npts) {
   const Variant* v = nullptr;
   if (field == FIELD_C128) {
-    // lane-group for few points from n = 7 (d > 4; n = 8, d = 8, 1000 points:
-    // 13 against 50 on two lanes) and where no register kernel is compiled
-    // (n >= 13; n = 12, d > 4; n >= 9, d > 8); at n = 11, d = 8, 10^5 points
-    // the register kernel takes 686, the best lane-group one 971.  For d = 5, 6
-    // the lane-group kernels, three waves per SIMD there, hold out longer (n = 11,
-    // d = 6: 64 against 96 at 8192 points, 92 against 99 at 12000; n = 10: 35
-    // against 53 at 5000, n = 8: 20 against 22 at 4096)
-    const bool mid = d == 5 || d == 6;
-    const int64_t few = mid && n == 11    ? 3 * kGroupPts
-                        : mid && n >= 9   ? kGroupPts * 3 / 2
-                        : n >= 9          ? kGroupPts
-                        : n == 8          ? (d > 8 || mid ? kGroupPts : d > 4 ? kGroupPts / 2 : kGroupPts / 4)
-                        : n == 7 && d > 4 ? kGroupPts / 4
-                                          : 0;
-    v = register_c128(n, d, npts);
-    if (!v || npts <= few) v = lane_group_c128(n, d, npts);
+    v = register_c128(n, d);
+    if (!v) v = lane_group_c128(n, d);
   } else {
     // lane-group from n = 8 (d > 4) for few points, at n = 11 up to
     // kFourLanePts (d = 6, 10^4 points: 44 against 49), and there for d > 6 at

@@ -115,23 +115,16 @@ struct Request {
   bool done = false;
 };
 
-// the kernel a request's own size selects over C; over Z_p, where every kernel
-// gives the same residues, the batch's size decides (null)
-const Variant* request_variant(const bg_group& g) {
-  return g.field == BG_FIELD_C128 ? choose_variant(g.field, g.n, g.d, g.npts) : nullptr;
-}
-
 struct Batch {
   int field = 0, n = 0, d = 0;
   uint32_t p = 0;
-  const Variant* variant = nullptr;
   std::vector<Request*> reqs;
   int64_t npts = 0, cols = 0, off = -1, bytes = 0;
   int stream = 0;
   hipEvent_t ev = nullptr;
   int rc = BG_OK;
   bool same_key(const bg_group& g) const {
-    return g.field == field && g.n == n && g.d == d && (field == BG_FIELD_C128 ? request_variant(g) == variant : g.p == p);
+    return g.field == field && g.n == n && g.d == d && (field == BG_FIELD_C128 || g.p == p);
   }
 };
 
@@ -187,7 +180,6 @@ std::vector<std::unique_ptr<Batch>> form_batches(bg_server* s, int slots) {
         b->n = r->g.n;
         b->d = r->g.d;
         b->p = r->g.p;
-        b->variant = request_variant(r->g);
       }
       r->col = b->npts;
       b->npts += r->g.npts;
@@ -245,7 +237,7 @@ void launch_batch(bg_server* s, Batch& b) {
     LaunchSpec spec;
     FpConst k{};
     if (b.field == BG_FIELD_FP) k = make_fp_const(b.p);
-    rc = prepare(b.field, b.n, b.d, b.npts, b.cols, mom, pol, out, sts, k, spec, b.variant);
+    rc = prepare(b.field, b.n, b.d, b.npts, b.cols, mom, pol, out, sts, k, spec);
     if (rc == BG_OK) rc = enqueue(spec, st);
   }
   if (rc == BG_OK) {
