@@ -146,8 +146,24 @@ struct Loader<C128Field<DL, L>> {
   template <int M>
   __device__ static cplx get(const LaunchArgs& a, const void* base, int l, int mu, int64_t q,
                              uint32_t&) {
-    return fix<M>(a, mu,
-                  static_cast<const double2*>(base)[((int64_t)l * a.d + (mu < a.d ? mu : 0)) * a.ld + q]);
+    const bool in = mu < a.d;
+    if constexpr (DL == 3 && L == 2) {
+      return fix<M>(a, mu, static_cast<const double2*>(base)[((int64_t)l * a.d + (in ? mu : 0)) * a.ld + q]);
+    } else {
+      // fix() written out: behind a call the selects come in another order, and
+      // the kernels at the edge of the register file spill by it.  Two-lane
+      // kernels of three components are the one shape that takes the call
+      // better.  Bytes spilled and us of 512000 points, written out against the
+      // call: n = 8, d = 9 (four lanes) 184 and 1169 against 280 and 1243, n = 6,
+      // d = 10 (two lanes) 136 and 372 against 148 and 382; n = 8, d = 5 (two lanes
+      // of three) 256 and 578 against 184 and 546.
+      const double2 v = static_cast<const double2*>(base)[((int64_t)l * a.d + (in ? mu : 0)) * a.ld + q];
+      const bool alt = M == MetricAlt || (M == MetricRT && a.metric != 0);
+      double re = in ? v.x : 0.0, im = in ? v.y : 0.0;
+      const bool rot = mu == 0 || (alt && mu >= 2 && (mu & 1) == 0);  // times i, exactly
+      const double r2 = rot ? -im : re, i2 = rot ? re : im;
+      return cplx{r2, i2};
+    }
   }
   // the component of a value that was read
   template <int M>
@@ -688,12 +704,26 @@ struct Recursion {
   }
 };
 
-// One point's result: the amplitude by the group's first lane, or the root
-// current by all of them, and the status.
-template <class Fld, int DL, int L>
-__device__ __forceinline__ void store_point(const LaunchArgs& a, int64_t q, bool valid, int s, uint32_t bad,
-                                            bool singular, typename Fld::S res, typename Fld::E (&kroot)[DL]) {
+// W = minimum waves per SIMD the register allocation must allow (1: the whole
+// register file for one wave; 2: at most 256 registers per lane).
+template <class Fld, int N, int DL, int L, int BLOCK, bool LT, int W>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W)))
+void bg_recursion_kernel(LaunchArgs a) {
+  using Rec = Recursion<Fld, N, DL, L, LT>;
+  __shared__ typename Rec::template Lds<BLOCK> lds;
+  const int64_t g = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  const int s = (int)(g % L);
+  const int64_t q0 = g / L;
+  const bool valid = q0 < a.npts;
+  const int64_t q = valid ? q0 : a.npts - 1;  // tail groups recompute the last point
+  uint32_t bad = 0;
+  bool singular = false;
+  typename Fld::S res;
+  typename Fld::E kroot[DL];
   if constexpr (Fld::exact) {
+    Fld F(a.fp, s);
+    if (a.metric != 0) Rec::template run<BLOCK, MetricAlt>(F, a, q, s, bad, singular, res, kroot, &lds);
+    else Rec::template run<BLOCK, MetricMM>(F, a, q, s, bad, singular, res, kroot, &lds);
     if constexpr (L > 1)
       bad = group_sum<L>(bad, [](uint32_t x, uint32_t y) { return x > y ? x : y; },
                          [](auto ctrl, uint32_t v) { return dpp_u32<decltype(ctrl)::value>(v); });
@@ -731,6 +761,8 @@ __device__ __forceinline__ void store_point(const LaunchArgs& a, int64_t q, bool
       if (a.status) a.status[q] = st;
     }
   } else {
+    Fld F(s);
+    Rec::template run<BLOCK, MetricRT>(F, a, q, s, bad, singular, res, kroot, &lds);
     if (a.cur) {
       if (valid) {
 #pragma unroll
@@ -762,33 +794,6 @@ __device__ __forceinline__ void store_point(const LaunchArgs& a, int64_t q, bool
   }
 }
 
-// W = minimum waves per SIMD the register allocation must allow (1: the whole
-// register file for one wave; 2: at most 256 registers per lane).
-template <class Fld, int N, int DL, int L, int BLOCK, bool LT, int W>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W)))
-void bg_recursion_kernel(LaunchArgs a) {
-  using Rec = Recursion<Fld, N, DL, L, LT>;
-  __shared__ typename Rec::template Lds<BLOCK> lds;
-  const int64_t g = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  const int s = (int)(g % L);
-  const int64_t q0 = g / L;
-  const bool valid = q0 < a.npts;
-  const int64_t q = valid ? q0 : a.npts - 1;  // tail groups recompute the last point
-  uint32_t bad = 0;
-  bool singular = false;
-  typename Fld::S res;
-  typename Fld::E kroot[DL];
-  if constexpr (Fld::exact) {
-    Fld F(a.fp, s);
-    if (a.metric != 0) Rec::template run<BLOCK, MetricAlt>(F, a, q, s, bad, singular, res, kroot, &lds);
-    else Rec::template run<BLOCK, MetricMM>(F, a, q, s, bad, singular, res, kroot, &lds);
-  } else {
-    Fld F(s);
-    Rec::template run<BLOCK, MetricRT>(F, a, q, s, bad, singular, res, kroot, &lds);
-  }
-  store_point<Fld, DL, L>(a, q, valid, s, bad, singular, res, kroot);
-}
-
 // ---------------------------------------------------------------------------
 // streaming form: resident blocks, each point's inputs read one point ahead
 // ---------------------------------------------------------------------------
@@ -817,6 +822,43 @@ constexpr bool stream_pays() {
   return !Fld::exact && LT && DL >= 2 && held > 200 && held + ahead <= 400;
 }
 
+// A point's result, as at the end of bg_recursion_kernel (which has it written
+// out: behind a call the registers of the recursion's last range fall
+// differently, and its kernels that spill do so more: n = 8, d = 9 184 bytes
+// against 180, 15514 points 39.7 against 39.0 us).
+template <int DL>
+__device__ __forceinline__ void store_point(const LaunchArgs& a, int64_t q, bool valid, int s, bool singular, cplx res,
+                                            cplx (&kroot)[DL]) {
+  if (a.cur) {
+    if (valid) {
+#pragma unroll
+      for (int c = 0; c < DL; ++c) {
+        const int mu = s * DL + c;
+        if (mu < a.d) {
+          // component 0 back from its factor i: K^0 = -i (i K^0)
+          const cplx k = mu == 0 ? cplx{kroot[c].im, -kroot[c].re} : kroot[c];
+          double2 o;
+          o.x = singular ? __builtin_nan("") : 2.0 * k.re;
+          o.y = singular ? __builtin_nan("") : 2.0 * k.im;
+          static_cast<double2*>(a.cur)[(int64_t)mu * a.ld + q] = o;
+        }
+      }
+      if (a.status && s == 0) a.status[q] = singular ? PT_SINGULAR : PT_OK;
+    }
+  } else if (valid && s == 0) {
+    double2 o;
+    if (singular) {
+      o.x = __builtin_nan("");
+      o.y = __builtin_nan("");
+    } else {
+      o.x = -2.0 * res.re;
+      o.y = -2.0 * res.im;
+    }
+    static_cast<double2*>(a.out)[q] = o;
+    if (a.status) a.status[q] = singular ? PT_SINGULAR : PT_OK;
+  }
+}
+
 template <class Fld, int N, int DL, int L, int BLOCK, bool LT, int W>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W)))
 void bg_recursion_stream_kernel(LaunchArgs a) {
@@ -841,7 +883,7 @@ void bg_recursion_stream_kernel(LaunchArgs a) {
     // group would keep a single L2 channel busy for microseconds
     Rec::template run<BLOCK, MetricRT, true>(F, a, q, s, bad, singular, res, kroot, &lds, &raw,
                                              q0 + step < a.npts ? q0 + step : q);
-    store_point<Fld, DL, L>(a, q, valid, s, bad, singular, res, kroot);
+    store_point<DL>(a, q, valid, s, singular, res, kroot);
   }
 }
 
