@@ -198,13 +198,16 @@ static const Variant* lane_group_c128(int n, int d) {
 // padded), 32 at n = 14 (d = 6: 676 against 731), where d = 7, 8 takes padded
 // rows (2 10^4 points: 175 against 194); two lanes per item for few points
 // (n = 11, d = 8, 1000 points: 22 against 29 with 16 lanes per point) and for
-// d = 9, 10 from n = 12 on (n = 14, 10^5 points: 1039 against 1070).
+// d = 9, 10 from n = 12 on (n = 14, 10^5 points: 1039 against 1070).  At n = 14,
+// d = 7, 8 the 64 lanes of a point end at 3072 points, what the LDS of 256 CUs
+// holds of them (3000 points: 44 against 48 on 32 lanes, 4000: 54 against 48; with
+// a prime of large 2^32 mod p 49 against 51 and 60 against 51).
 static const Variant* lane_group_fp(int n, int d, int64_t npts) {
   if (npts <= kGroupPts / 2) {
     if (d <= 4) return lane_group_variant(FIELD_FP, 4, 32, 1, false);
     return lane_group_variant(FIELD_FP, d <= 8 ? 8 : 10, 32, 2, false);
   }
-  if (npts <= kGroupPts) {
+  if (npts <= (n >= 14 && (d == 7 || d == 8) ? kGroupPts * 3 / 4 : kGroupPts)) {
     if (d <= 4) return lane_group_variant(FIELD_FP, 4, n >= 12 ? 32 : 16, 1, false);
     if (d > 8) return lane_group_variant(FIELD_FP, 10, n >= 13 ? 32 : 16, 2, false);
     if (d <= 6 && n >= 13) return lane_group_variant(FIELD_FP, 6, 32, 1, false);
@@ -221,8 +224,11 @@ static const Variant* lane_group_fp(int n, int d, int64_t npts) {
 // 128000 points: 161 against 245), d = 7, 8 from n = 6 on (n = 8, 128000: 175
 // against 294), d = 5, 6 from n = 9 on (n = 9, 128000: 275 against 277, 1000
 // points 1.5 times faster), any d from n = 11 on; else two (n = 8, d = 4, 512000:
-// 294 against 443).  n = 5, d = 7, 8 stay on two: the four-lane kernel is faster
-// at most sizes (256000: 67 against 70), not at 32000 (11.4 against 10.4).
+// 294 against 443).  Four lanes lose from 16385 to 32768 points, where their
+// waves share a SIMD and those of two lanes still run one to a SIMD (n = 6, d = 8,
+// 20000 points: 16.1 against 14.5, 48000: 22.4 against 28.6; n = 6, d = 9 up to
+// 10^5 points, 64000: 48.5 against 45.6, 256000: 171 against 191).  n = 5, d = 7, 8
+// stay on two: the gain beyond that window is small (256000: 67 against 70).
 static const Variant* register_c128(int n, int d) {
   const Variant* four = register_variant(FIELD_C128, n, d, 4);
   const Variant* two = register_variant(FIELD_C128, n, d, 2);
