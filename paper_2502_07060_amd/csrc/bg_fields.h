@@ -67,12 +67,12 @@ struct FpField {
   }
 
   __device__ __forceinline__ E prime0(E x) const {
-    if constexpr (L == 1) return -x;
-    else return time_lane ? -x : x;
+    if constexpr (L == 1) return sub32(0, x);
+    else return time_lane ? sub32(0, x) : x;
   }
   __device__ __forceinline__ E esub(E a, E b) const { return fp_sub(a, b, k); }
   __device__ __forceinline__ E eadd(E a, E b) const { return fp_add(a, b, k); }
-  __device__ __forceinline__ S sneg(S a) const { return -a; }
+  __device__ __forceinline__ S sneg(S a) const { return sub32(0, a); }
   __device__ __forceinline__ S szero() const { return 0; }
   __device__ __forceinline__ A azero() const { return 0; }
 
@@ -135,7 +135,7 @@ struct FpField {
           u = 2;
         }
       }
-      t = group_sum<L>(t, [](A a, A b) { return a + b; },
+      t = group_sum<L>(t, [](A a, A b) { return add64(a, b); },
                        [](auto ctrl, A v) { return (A)dpp_u64<decltype(ctrl)::value>((uint64_t)v); });
       u *= L;
     }

@@ -572,8 +572,8 @@ __global__ __launch_bounds__(256) void state_sum_fp_kernel(StateSumArgs a) {
     L[mu] = fp_from_canonical(l, F);
     Rv[mu] = fp_from_canonical(r, F);
   }
-  L[0] = -L[0];  // primed: sum_mu L'_mu x_mu = -(L . x)
-  Rv[0] = -Rv[0];
+  L[0] = sub32(0, L[0]);  // primed: sum_mu L'_mu x_mu = -(L . x)
+  Rv[0] = sub32(0, Rv[0]);
   // (e.K_L)(e~.K_R) = (-(e.K_L))(-(e~.K_R)); each dot is reduced to t 2^-32
   // (below 1.5 2^30), the products of two such are summed in int64 (2^-64) and
   // reduced once more (2^-96), and one product with 2^128 restores S

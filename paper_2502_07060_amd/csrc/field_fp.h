@@ -52,7 +52,18 @@ struct FpConst {
 
 __device__ __forceinline__ int64_t mul64(int32_t a, int32_t b) { return (int64_t)a * (int64_t)b; }
 
-__device__ __forceinline__ int64_t mad64(int32_t a, int32_t b, int64_t c) { return (int64_t)a * (int64_t)b + c; }
+// A residue that a caller passes may be any 32-bit value.  One >= p only marks
+// its point (the result is the sentinel) and goes through the arithmetic as it
+// is: one minimum a load to keep it below p costs up to a third of the speed
+// (n = 10, d = 4..6, 128000 points and more: 0.65 to 0.75 of it).  Its sums pass
+// the bounds, so sums, differences and negations that it can reach are formed
+// modulo 2^32 and 2^64, in the same instructions.
+__device__ __forceinline__ int64_t mad64(int32_t a, int32_t b, int64_t c) {
+  return (int64_t)((uint64_t)mul64(a, b) + (uint64_t)c);
+}
+__device__ __forceinline__ int64_t add64(int64_t a, int64_t b) { return (int64_t)((uint64_t)a + (uint64_t)b); }
+__device__ __forceinline__ int32_t add32(int32_t a, int32_t b) { return (int32_t)((uint32_t)a + (uint32_t)b); }
+__device__ __forceinline__ int32_t sub32(int32_t a, int32_t b) { return (int32_t)((uint32_t)a - (uint32_t)b); }
 
 // T congruent, |result| < 2^31 h + 2^32.  Formed as T + hi c32 (modulo 2^64)
 // with hi then taken off the high word: one multiply-add into T itself and
@@ -111,16 +122,17 @@ __device__ __forceinline__ int32_t fp_norm(int32_t x, const FpConst& F) {
 }
 
 __device__ __forceinline__ int32_t fp_add(int32_t a, int32_t b, const FpConst& F) {
-  return fp_norm(a + b, F);  // |a + b| <= 2h < 2^31
+  return fp_norm(add32(a, b), F);  // |a + b| <= 2h < 2^31
 }
 __device__ __forceinline__ int32_t fp_sub(int32_t a, int32_t b, const FpConst& F) {
-  return fp_norm(a - b, F);
+  return fp_norm(sub32(a, b), F);
 }
 
-// canonical input residue x in [0, p) -> balanced representative
+// canonical input residue x in [0, p) -> balanced representative (any other x:
+// some int32)
 __device__ __forceinline__ int32_t fp_from_canonical(uint32_t x, const FpConst& F) {
   const int32_t v = (int32_t)x;
-  return v - (((F.h - v) >> 31) & F.p);
+  return sub32(v, v > F.h ? F.p : 0);
 }
 
 __device__ __forceinline__ uint32_t fp_to_canonical(int32_t v, const FpConst& F) {
