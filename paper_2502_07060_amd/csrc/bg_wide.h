@@ -190,7 +190,6 @@ struct WideRecursion {
   __device__ __forceinline__ int rid(int i, int j) const { return range_idx(N, i, j); }
   __device__ __forceinline__ E& Jat(int r, int c) const { return Jt[r * kS + c]; }
   __device__ __forceinline__ E& Mat(int l, int c) const { return Mt[l * kS + c]; }
-  __device__ __forceinline__ E& Mlo(int l, int c) const { return Ml[l * kS + c]; }
   // one table row into registers with 16-byte LDS reads where the layout
   // allows (complex elements are 16 bytes; F_p rows of a padded layout start
   // on 16-byte boundaries)
@@ -599,7 +598,7 @@ struct WideRecursion {
         }
         range_sum(F, K, nDs, per);
         if (act && u == 0) {  // the range's first item finishes it
-          const int id = rid(r, r + m - 1);
+          [[maybe_unused]] const int id = rid(r, r + m - 1);
           S nDhS;
           if constexpr (kFp) {
             nDhS = range_dh(F, nDs);
@@ -610,16 +609,7 @@ struct WideRecursion {
             constexpr double kPart = 0.5 / Fld::kL;  // -Dh(S) / LC, the lanes' share
             nDhS = cplx{kPart * nDs.re, kPart * nDs.im};
           }
-          if (m < N) {
-            if constexpr (!kFp) inv2 = nDht[id];
-            nDht[id] = nDhS;
-            E Jn[DL];
-#pragma unroll
-            for (int c = 0; c < DL; ++c) {
-              Jn[c] = F.mul(F.finish(K[c]), inv2);
-              Jat(id, co + c) = Jn[c];
-            }
-          } else {
+          if (kFp || m == N) {  // the root; over F_p nothing else gets here
             E Kf[DL], en[DL];
 #pragma unroll
             for (int c = 0; c < DL; ++c) {
@@ -629,6 +619,11 @@ struct WideRecursion {
             result = F.ndot_u(en, Kf);
 #pragma unroll
             for (int c = 0; c < DL; ++c) kroot[c] = Kf[c];
+          } else if constexpr (!kFp) {
+            inv2 = nDht[id];
+            nDht[id] = nDhS;
+#pragma unroll
+            for (int c = 0; c < DL; ++c) Jat(id, co + c) = F.mul(F.finish(K[c]), inv2);
           }
         }
       }
