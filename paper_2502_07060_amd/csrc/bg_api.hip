@@ -198,10 +198,14 @@ static const Variant* lane_group_c128(int n, int d) {
 // padded), 32 at n = 14 (d = 6: 676 against 731), where d = 7, 8 takes padded
 // rows (2 10^4 points: 175 against 194); two lanes per item for few points
 // (n = 11, d = 8, 1000 points: 22 against 29 with 16 lanes per point) and for
-// d = 9, 10 from n = 12 on (n = 14, 10^5 points: 1039 against 1070).  At n = 14,
-// d = 7, 8 the 64 lanes of a point end at 3072 points, what the LDS of 256 CUs
-// holds of them (3000 points: 44 against 48 on 32 lanes, 4000: 54 against 48; with
-// a prime of large 2^32 mod p 49 against 51 and 60 against 51).
+// d = 9, 10 from n = 12 on (n = 14, 10^5 points: 1039 against 1070), where the
+// LDS holds 6144 points of n = 13 with two lanes and 8192 with one (7000 points: 77
+// against 76, with a prime of large 2^32 mod p 87 against 79), and at n = 14 one
+// lane and 32 items keep up to 12288 points (6000: 79 against 76, such a prime 88
+// against 80; 12000: 162 against 158, 181 against 170).  At n = 14, d = 7, 8 the 64
+// lanes of a point end at 3072 points, what the LDS of 256 CUs holds of them (3000
+// points: 44 against 48 on 32 lanes, 4000: 54 against 48; such a prime 49 against 51
+// and 60 against 51).
 static const Variant* lane_group_fp(int n, int d, int64_t npts) {
   if (npts <= kGroupPts / 2) {
     if (d <= 4) return lane_group_variant(FIELD_FP, 4, 32, 1, false);
@@ -213,7 +217,11 @@ static const Variant* lane_group_fp(int n, int d, int64_t npts) {
     if (d <= 6 && n >= 13) return lane_group_variant(FIELD_FP, 6, 32, 1, false);
     return lane_group_variant(FIELD_FP, 8, d > 6 && n >= 13 ? 32 : 16, 2, false);
   }
-  if (d > 8) return lane_group_variant(FIELD_FP, 10, 16, n >= 12 ? 2 : 1, false);
+  if (d > 8) {
+    if (n >= 14 && npts <= 3 * kGroupPts) return lane_group_variant(FIELD_FP, 10, 32, 1, false);
+    const bool one = n < 12 || (n == 13 && npts > kGroupPts * 3 / 2 && npts <= 2 * kGroupPts);
+    return lane_group_variant(FIELD_FP, 10, 16, one ? 1 : 2, false);
+  }
   const int dmax = d <= 4 ? 4 : d <= 6 ? 6 : 8;
   const bool items32 = n >= 14 && (dmax > 4 || npts <= kManyPts / 2);
   return lane_group_variant(FIELD_FP, dmax, items32 ? 32 : 16, 1, items32 && dmax == 8);
