@@ -270,7 +270,11 @@ const Variant* default_variant(int field, int n, int d, int64_t npts) {
     // kFourLanePts (d = 6, 10^4 points: 44 against 49), and there for d > 6 at
     // any size (d = 8, 10^5 points: 337 against 599: the register kernel
     // spills) and for d <= 4 from kManyPts on (10^5 points: 201 against 211); at
-    // n = 10, d <= 4 up to three times kGroupPts (12000 points: 29 against 34)
+    // n = 10, d <= 4 up to three times kGroupPts (12000 points: 29 against 34).  The
+    // lines are those of 2^31 - 19; primes of large 2^32 mod p take them too, though
+    // their register kernels spill at n = 10, d > 6 and n = 11, where a lane-group
+    // kernel would be faster (64000 points: n = 10, d = 8 192 against 244, n = 11,
+    // d = 4 152 against 266)
     const int64_t few = n == 11           ? (d > 6 ? INT64_MAX : kFourLanePts)
                         : n == 10         ? (d > 6 ? 2 * kGroupPts : d <= 4 ? 3 * kGroupPts : kGroupPts)
                         : n == 9          ? kGroupPts

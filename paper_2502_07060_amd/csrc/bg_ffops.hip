@@ -50,7 +50,7 @@ struct ContractArgs {
 // Before, y lay in an 8 x 8 array behind run-time guards for J, K <= 8 (each
 // load waited for in a block of its own), and larger J or K read y once per
 // row of x after a pass over all inputs for the status.  Events by I x J x K,
-// before and now: 2^20 of 6x6x6 247 -> 100 us (4.5 TB/s, a large copy
+// before and now: 2^20 of 6x6x6 256 -> 100 us (4.5 TB/s, a large copy
 // reaches 4.9); 150001 of 6x36x6 660 -> 72 us.
 //
 // YB: y per event; else one y for all events, read through scalar loads.

@@ -804,7 +804,7 @@ void bg_recursion_kernel(LaunchArgs a) {
 // points, and a point's inputs are read while the point before it is computed,
 // into registers that the recursion leaves free (accumulation registers, which
 // loads can write directly).  2^20 points of n = 8, d = 4: 1.43 M -> 1.26 M
-// cycles, 620 -> 591 us (at a lower clock: FP64 at this rate is power limited);
+// cycles, 600 -> 556 us (at a lower clock: FP64 at this rate is power limited);
 // n = 7 d = 4 and d = 8 203 -> 187 us and 188 -> 173 us (5 and 2 * 10^5
 // points), n = 6 d = 6 160 -> 146 us, n = 5 d = 8 134 -> 122 us.
 //
