@@ -113,7 +113,7 @@ struct Loader;
 
 template <int DL, int L, bool SC>
 struct Loader<FpField<DL, L, SC>> {
-  template <int M>
+  template <int M, bool = false>
   __device__ static int32_t get(const LaunchArgs& a, const void* base, int l, int mu, int64_t q,
                                 uint32_t& maxraw) {
     const bool in = mu < a.d;
@@ -143,20 +143,21 @@ struct Loader<FpField<DL, L, SC>> {
 
 template <int DL, int L>
 struct Loader<C128Field<DL, L>> {
-  template <int M>
+  template <int M, bool CALL = false>
   __device__ static cplx get(const LaunchArgs& a, const void* base, int l, int mu, int64_t q,
                              uint32_t&) {
     const bool in = mu < a.d;
-    if constexpr (DL == 3 && L == 2) {
+    if constexpr (CALL) {
       return fix<M>(a, mu, static_cast<const double2*>(base)[((int64_t)l * a.d + (in ? mu : 0)) * a.ld + q]);
     } else {
       // fix() written out: behind a call the selects come in another order, and
-      // the kernels at the edge of the register file spill by it.  Two-lane
-      // kernels of three components are the one shape that takes the call
-      // better.  Bytes spilled and us of 512000 points, written out against the
-      // call: n = 8, d = 9 (four lanes) 184 and 1169 against 280 and 1243, n = 6,
-      // d = 10 (two lanes) 136 and 372 against 148 and 382; n = 8, d = 5 (two lanes
-      // of three) 256 and 578 against 184 and 546.
+      // the kernels at the edge of the register file spill by it.  n = 8 with
+      // two lanes of three components is the one shape that takes the call
+      // better (Recursion::kLoadCall).  Bytes spilled and us of 512000 points,
+      // written out against the call: n = 8, d = 9 (four lanes) 180 and 1155 against
+      // 280 and 1243, n = 6, d = 10 (two lanes) 124 and 363 against 148 and 382;
+      // n = 8, d = 5 256 and 578 against 184 and 546.  n = 5, d = 6, 700000 points:
+      // 117.5 against 119.0.
       const double2 v = static_cast<const double2*>(base)[((int64_t)l * a.d + (in ? mu : 0)) * a.ld + q];
       const bool alt = M == MetricAlt || (M == MetricRT && a.metric != 0);
       double re = in ? v.x : 0.0, im = in ? v.y : 0.0;
@@ -279,6 +280,8 @@ struct Recursion {
   using R = Ranges<N>;
   static constexpr int NCUR = R::ncur;   // non-root currents
   static constexpr int NP = R::nprop;    // propagators
+  // complex loads: how Loader::get is compiled
+  static constexpr bool kLoadCall = N == 7 && DL == 3 && L == 2;
   // F_p schedule for small fold constants (FpField)
   static constexpr bool kSmallFold = []() { if constexpr (Fld::exact) return Fld::kSC; else return false; }();
 
@@ -376,8 +379,8 @@ struct Recursion {
           k[c] = Loader<Fld>::template fix<M>(a, mu0 + c, raw->k[l][c]);
           J[R::idx(l, l)][c] = Loader<Fld>::template fix<M>(a, mu0 + c, raw->e[l][c]);
         } else {
-          k[c] = Loader<Fld>::template get<M>(a, a.momenta, l, mu0 + c, q, bad);
-          J[R::idx(l, l)][c] = Loader<Fld>::template get<M>(a, a.pols, l, mu0 + c, q, bad);
+          k[c] = Loader<Fld>::template get<M, kLoadCall>(a, a.momenta, l, mu0 + c, q, bad);
+          J[R::idx(l, l)][c] = Loader<Fld>::template get<M, kLoadCall>(a, a.pols, l, mu0 + c, q, bad);
         }
       }
       k[0] = F.prime0(k[0]);
@@ -392,7 +395,7 @@ struct Recursion {
       }
     });
 #pragma unroll
-    for (int c = 0; c < DL; ++c) epsn[c] = Loader<Fld>::template get<M>(a, a.pols, N, mu0 + c, q, bad);
+    for (int c = 0; c < DL; ++c) epsn[c] = Loader<Fld>::template get<M, kLoadCall>(a, a.pols, N, mu0 + c, q, bad);
     if constexpr (STREAM) {
       split_barrier();  // the reads start here, ahead of the recursion
       raw->read(a, qnext, mu0);
